@@ -38,14 +38,16 @@ __device__ __forceinline__ void reduce_body(ReduceArgs a, int b) {
     const int64_t lo = a.bin_off[b], hi = a.bin_off[b + 1];
     const int64_t n = hi - lo;
     if (!a.layout_g) {
-      // HNEMA-only: parts [p][slot][mu], already summed over each part's steps
+      // HNEMA-only: parts [p][sub][slot][mu], already summed over each part's steps
       double s3[3] = {0.0, 0.0, 0.0};
       const int per_part = (int)(n * 3);
       for (int p = 0; p < a.n_parts; ++p) {
-        const float* base = a.in + ((int64_t)p * a.M_pad + lo) * 3;
+        const float* base = a.in + ((int64_t)p * a.n_sub * a.M_pad + lo) * 3;
         int mu = tid % 3;                       // e % 3, and 256 % 3 == 1
         for (int e = tid; e < per_part; e += 256) {
-          const double val = (double)base[e];
+          float part = base[e];
+          for (int q = 1; q < a.n_sub; ++q) part += base[(int64_t)q * a.M_pad * 3 + e];
+          const double val = (double)part;
           if (mu == 0) s3[0] += val; else if (mu == 1) s3[1] += val; else s3[2] += val;
           mu = (mu == 2) ? 0 : mu + 1;
         }

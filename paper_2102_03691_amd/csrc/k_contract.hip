@@ -817,9 +817,11 @@ __global__ void __launch_bounds__(256) k_gemm_fixup(const float* __restrict__ ws
 // Plan of the lockstep split for n_tiles tiles of S stages on G = n_cu
 // work-groups; false if it would not shorten the launch (estimated in
 // stage-times of one CU) by at least min_gain, or the workspace is short.
+// *stages receives that estimate for the launch as it will run.
 static bool plan_split(int64_t n_tiles, int S, int G, int64_t slot_floats, int64_t ws_floats, double min_gain,
-                       SplitPlan* sp) {
+                       SplitPlan* sp, double* stages) {
   constexpr int MIN_PIECE = 8;                                   // stages per piece
+  *stages = (double)((n_tiles + G - 1) / std::max(G, 1)) * S;
   if (G < 2 || n_tiles < 1) return false;
   const int64_t q = n_tiles / G;
   const int R = (int)(n_tiles % G);
@@ -858,14 +860,277 @@ static bool plan_split(int64_t n_tiles, int S, int G, int64_t slot_floats, int64
   if ((int64_t)p.m * R * slot_floats > ws_floats) return false;
   const double plain = (double)(q + 1) * S, split = (double)q * S + span;
   if (split > (1.0 - min_gain) * plain) return false;
+  *stages = split;
   *sp = p;
   return true;
+}
+
+// ------------------------------------------------- one channel per wave
+// The contraction of small systems.  Few tiles of the kernels above leave
+// most CUs idle (6912 modes at T = 64: 27 tiles on 256 CUs), so here a
+// work-group takes only MB row blocks (32 slots each) x one t-block of 32
+// steps and its four waves take one channel each: 16 times as many
+// work-groups as 128 x 4 tiles, with the four accumulators of a (slot, step)
+// in four waves that meet in the epilogue through LDS.  Every accumulator
+// adds its products in the same order as in the tiles above, so the results
+// are the same bits whichever kernel runs; MODE carries over the sums that
+// are not one running sum over k:
+//   1: the pieces of the split schedule (each piece summed from zero, the
+//      pieces added in piece order), without its workspace and its fences;
+//   2: the direction split (channels 1 .. 3 restart at every third of k; the
+//      brackets of thirds 0 and 1 wait in registers).
+// Bound: latency of the operand loads (a k-stage is only 192 cycles of BF16
+// products per wave), so a wave keeps PD k-stages of its channel's B operand
+// in registers, each refilled as soon as it is consumed, and E is staged PD
+// stages at a time, double-buffered in LDS.  Measured per launch: 6912 modes
+// at T = 64, FP32, direction split 1624 -> 230 us; 1500 modes at T = 96,
+// split BF16 (8 pieces a tile) 238 -> 23 us.
+constexpr int CHAN_PD = 4;   // k-stages per LDS buffer and in flight per wave
+
+// The tiles (rows row blocks x tbs t-blocks each, numbered as in k_gemm) from
+// `first` on that a k_gemm_chan launch takes.
+struct ChanTiles {
+  int64_t first;
+  int rows, tbs;
+};
+
+template <int PREC, int MB, bool TR, int MODE>
+__global__ void __launch_bounds__(256, 2) k_gemm_chan(GemmGeom g, SplitPlan sp, ChanTiles ct) {
+  using C = GemmCfg<PREC>;
+  constexpr int PD = CHAN_PD;
+  __shared__ u32x4 lds[2][MB][PD * SU];
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+  const int c = __builtin_amdgcn_readfirstlane(tid >> 6);       // channel
+  const int S = g.n_stages;
+  const int64_t per_blk = C::UNITS_PER_DOF2 * g.K_pad;
+  // the t-blocks of a row block are neighbours (one XCD), sharing its rows of E
+  const int64_t lin = wg_linear(blockIdx.x, gridDim.x);
+  const int per_tile = ct.rows / MB * ct.tbs;
+  const int64_t tile = ct.first + lin / per_tile;
+  const int sub = (int)(lin % per_tile);
+  const int tb = (int)(tile % g.n_ntiles) * ct.tbs + sub % ct.tbs;
+  const int64_t rb0 = tile / g.n_ntiles * ct.rows + sub / ct.tbs * MB;
+  const gu32x4* Eb = (const gu32x4*)g.E + rb0 * per_blk;
+  const gu32x4* Bw = (const gu32x4*)g.B + ((int64_t)c * g.ntb + tb) * per_blk;
+
+  f32x16 acc[MB], kept[MODE == 0 ? 1 : MODE][MB];   // MODE 1: sum of the pieces; 2: thirds 0, 1
+  auto zero = [&]() {
+#pragma unroll
+    for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[rb][j] = 0.f;
+  };
+  zero();
+  u32x4 ast[MB * PD], bq[PD][4];
+  auto load_A = [&](int s) {
+#pragma unroll
+    for (int q = 0; q < MB; ++q)
+#pragma unroll
+      for (int k = 0; k < PD; ++k) ast[q * PD + k] = (Eb + ((int64_t)q * per_blk + (int64_t)min(s + k, S - 1) * SU))[tid];
+  };
+  auto store_A = [&](int buf) {
+#pragma unroll
+    for (int q = 0; q < MB; ++q)
+#pragma unroll
+      for (int k = 0; k < PD; ++k) lds[buf][q][k * SU + tid] = ast[q * PD + k];
+  };
+  auto load_B = [&](int k, int s) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) bq[k][u] = (Bw + ((int64_t)min(s, S - 1) * SU + u * 64))[lane];
+  };
+  auto compute = [&](int buf, int k) {
+    if constexpr (C::BF) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        const bf16x8 bh = __builtin_bit_cast(bf16x8, bq[k][2 * kk]), bl = __builtin_bit_cast(bf16x8, bq[k][2 * kk + 1]);
+        bf16x8 ah[MB], al[MB];
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) {
+          ah[rb] = __builtin_bit_cast(bf16x8, lds[buf][rb][k * SU + (2 * kk) * 64 + lane]);
+          al[rb] = __builtin_bit_cast(bf16x8, lds[buf][rb][k * SU + (2 * kk + 1) * 64 + lane]);
+        }
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) acc[rb] = mm_bf16<TR>(ah[rb], bh, acc[rb]);
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) acc[rb] = mm_bf16<TR>(ah[rb], bl, acc[rb]);
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) acc[rb] = mm_bf16<TR>(al[rb], bh, acc[rb]);
+      }
+    } else if constexpr (C::F8X3) {
+      const i32x8 bh = cat8(bq[k][0], bq[k][1]), bl = cat8(bq[k][2], bq[k][3]);
+#pragma unroll
+      for (int rb = 0; rb < MB; ++rb) {
+        const u32x4* ar = &lds[buf][rb][k * SU + lane];
+        const i32x8 ah = cat8(ar[0], ar[64]), al = cat8(ar[128], ar[192]);
+        acc[rb] = mm_fp8<TR>(ah, bh, acc[rb]);
+        acc[rb] = mm_fp8<TR>(ah, bl, acc[rb]);
+        acc[rb] = mm_fp8<TR>(al, bh, acc[rb]);
+      }
+    } else if constexpr (C::F8) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        const i32x8 b = cat8(bq[k][2 * kk], bq[k][2 * kk + 1]);
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) {
+          const u32x4* ar = &lds[buf][rb][k * SU + kk * 128 + lane];
+          acc[rb] = mm_fp8<TR>(cat8(ar[0], ar[64]), b, acc[rb]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const f32x4 b = __builtin_bit_cast(f32x4, bq[k][kk]);
+        f32x4 a[MB];
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) a[rb] = __builtin_bit_cast(f32x4, lds[buf][rb][k * SU + kk * 64 + lane]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int rb = 0; rb < MB; ++rb) acc[rb] = mm_f32<TR>(a[rb][e], b[e], acc[rb]);
+      }
+    }
+  };
+  // before stage s: the end of a piece or of a third (the same for the whole work-group)
+  int piece = 0, next = MODE == 1 ? split_stage(sp, S, 1) : (MODE == 2 ? g.s3 : S);
+  auto boundary = [&]() {
+    if constexpr (MODE == 1) {
+#pragma unroll
+      for (int rb = 0; rb < MB; ++rb) kept[0][rb] = piece == 0 ? acc[rb] : kept[0][rb] + acc[rb];
+      zero();
+      ++piece;
+      next = split_stage(sp, S, piece + 1);
+    } else if constexpr (MODE == 2) {
+#pragma unroll
+      for (int rb = 0; rb < MB; ++rb) {
+        if (piece == 0) kept[0][rb] = acc[rb];
+        else kept[MODE - 1][rb] = acc[rb];
+      }
+      if (c > 0) zero();   // channel 0 (Xdot) runs on over the thirds
+      ++piece;
+      next += g.s3;
+    }
+  };
+
+  load_A(0);
+#pragma unroll
+  for (int k = 0; k < PD; ++k) load_B(k, k);
+  store_A(0);
+  __syncthreads();
+  int buf = 0;
+  for (int s0 = 0; s0 < S; s0 += PD, buf ^= 1) {
+    load_A(s0 + PD);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < PD; ++k) {
+      if (s0 + k < S) {
+        if (MODE != 0 && s0 + k == next) boundary();
+        compute(buf, k);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      load_B(k, s0 + k + PD);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    store_A(buf ^ 1);
+    __syncthreads();
+  }
+  if constexpr (MODE == 1) {
+    if (sp.m > 1)
+#pragma unroll
+      for (int rb = 0; rb < MB; ++rb) acc[rb] = kept[0][rb] + acc[rb];
+  }
+
+  // epilogue: Xdot of channel 0's wave to the others, J_n^mu in wave mu + 1
+  float* xs = reinterpret_cast<float*>(&lds[0][0][0]);           // [MB][16][64]
+  const int64_t ld = (int64_t)g.ntb * 32, t0 = (int64_t)tb * 32;
+  auto scaled = [&](f32x16 (&a)[MB]) {
+    if constexpr (is_fp8(PREC)) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const float cs = g.col_scale[c * ld + t0 + (TR ? acc_row(j, half) : (lane & 31))];
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) a[rb][j] *= cs;
+      }
+    }
+  };
+  auto emit = [&](f32x16 (&a)[MB], float* out) {
+#pragma unroll
+    for (int rb = 0; rb < MB; ++rb) {
+      const float* xr = xs + rb * 16 * 64 + lane;
+      if constexpr (TR) {
+        // the lane's 16 steps in register order, then the other half-wave's
+        float p = 0.f;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) p += xr[j * 64] * a[rb][j];
+        p += __shfl_xor(p, 32);
+        const int64_t slot = (rb0 + rb) * 32 + (lane & 31);
+        float f = 1.f;
+        if constexpr (is_fp8(PREC)) f = g.row_scale[slot] * g.row_scale[slot];
+        if (half == 0) out[((int64_t)tb * g.M_pad + slot) * 3 + c - 1] = p * f;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          const int64_t slot = (rb0 + rb) * 32 + acc_row(j, half);
+          float f = 1.f;
+          if constexpr (is_fp8(PREC)) f = g.row_scale[slot] * g.row_scale[slot];
+          out[((int64_t)(c - 1) * g.M_pad + slot) * ld + t0 + (lane & 31)] = xr[j * 64] * a[rb][j] * f;
+        }
+      }
+    }
+  };
+  scaled(acc);
+  if (c == 0) {
+#pragma unroll
+    for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) xs[(rb * 16 + j) * 64 + lane] = acc[rb][j];
+  }
+  __syncthreads();
+  if (c == 0) return;
+  if constexpr (MODE == 2) {
+    emit(acc, g.out + 2 * g.region);
+    scaled(kept[0]);
+    emit(kept[0], g.out);
+    scaled(kept[MODE - 1]);
+    emit(kept[MODE - 1], g.out + g.region);
+  } else {
+    emit(acc, g.out);
+  }
+}
+
+// Estimated microseconds of the two kernels, the rule between them: a row
+// block's products of one k-stage on one SIMD (four channels in a tile's wave,
+// one in k_gemm_chan's, which waits on its loads more often), and what the
+// pieces of a split tile cost (each released, and added by one work-group).
+// Measured (MB = 4 row blocks per tile wave): 48 tiles of 384 stages take
+// 2880 (FP32), 690 (split BF16) and 404 us (e4m3 hi/lo, 192 stages); the same
+// work one channel per wave 683, 322 and 144 us; 24 tiles cut into 10 pieces
+// of 9 stages 615 us in split BF16, one channel per wave 35 us.
+static double tile_us(int prec, double stages, int MB, int pieces) {
+  const double c = prec == PREC_FP32 ? 0.47 : (prec == PREC_FP8 ? 0.105 : (prec == PREC_FP8X3 ? 0.13 : 0.12));
+  return stages * 4 * MB * c + (pieces - 1) * 17.5 * MB;
+}
+static int chan_rows(int64_t n_units, int n_cu) { return n_units >= 4 * (int64_t)n_cu ? 2 : 1; }
+static double chan_us(int prec, int64_t n_units, int S, int n_cu) {
+  const double c = prec == PREC_FP32 ? 0.6 : (prec == PREC_FP8 ? 0.21 : (prec == PREC_FP8X3 ? 0.23 : 0.24));
+  const int MB = chan_rows(n_units, n_cu);
+  return 5.0 + (double)((n_units / MB + n_cu - 1) / n_cu) * MB * S * c;
+}
+
+template <int PREC, bool TR, int MODE>
+static hipError_t launch_chan(hipStream_t s, const GemmGeom& g, const SplitPlan& sp, const ChanTiles& ct,
+                              int64_t n_tiles, int n_cu) {
+  const int64_t units = n_tiles * ct.rows * ct.tbs;
+  if (chan_rows(units, n_cu) == 2)
+    hipLaunchKernelGGL((k_gemm_chan<PREC, 2, TR, MODE>), dim3((unsigned)(units / 2)), dim3(256), 0, s, g, sp, ct);
+  else
+    hipLaunchKernelGGL((k_gemm_chan<PREC, 1, TR, MODE>), dim3((unsigned)units), dim3(256), 0, s, g, sp, ct);
+  return hipGetLastError();
 }
 
 template <int PREC, int WM, int WT, int MB, bool TR>
 static hipError_t launch_gemm_shape(hipStream_t s, const void* E, const void* B, float* out, float* ws,
                                     int64_t ws_floats, int* tile_cnt, GemmGeom g, int n_mtiles, int n_cu,
-                                    int sched, int* used) {
+                                    int sched, int* used, int* n_sub) {
   constexpr int NREG = MB * 4 * 16;
   const int64_t n_tiles = (int64_t)n_mtiles * g.n_ntiles;
   g.total_iters = n_tiles * g.n_stages;
@@ -874,15 +1139,44 @@ static hipError_t launch_gemm_shape(hipStream_t s, const void* E, const void* B,
   g.out = out;
   // Lockstep split when the last round of tiles would leave CUs idle
   // (AUTO: only when it saves at least 5 %).
-  if ((sched == MHC_SCHED_SPLIT || sched == MHC_SCHED_AUTO) && tile_cnt) {
-    SplitPlan sp{};
-    if (plan_split(n_tiles, g.n_stages, n_cu, (int64_t)NREG * 256, ws_floats,
-                   sched == MHC_SCHED_AUTO ? 0.05 : 0.0, &sp)) {
-      sp.cnt = tile_cnt;
-      hipLaunchKernelGGL((k_gemm_split<PREC, WM, WT, MB, TR>), dim3((unsigned)n_cu), dim3(256), 0, s, ws, g, sp);
-      *used = MHC_SCHED_SPLIT;
-      return hipGetLastError();
+  SplitPlan sp{};
+  double stages = (double)((n_tiles + n_cu - 1) / std::max(n_cu, 1)) * g.n_stages;
+  const bool split = (sched == MHC_SCHED_SPLIT || sched == MHC_SCHED_AUTO) && tile_cnt &&
+                     plan_split(n_tiles, g.n_stages, n_cu, (int64_t)NREG * 256, ws_floats,
+                                sched == MHC_SCHED_AUTO ? 0.05 : 0.0, &sp, &stages);
+  // Too few tiles to fill the chip (in the last round, if the split has whole
+  // rounds before it): one channel per wave, with the split's pieces, whose
+  // sums are the same whoever adds them
+  const int64_t rest = split ? sp.R : n_tiles;
+  const int64_t units = rest * WM * MB * WT;
+  if (sched != MHC_SCHED_STREAMK &&
+      chan_us(PREC, units, g.n_stages, n_cu) <
+          tile_us(PREC, stages - (double)sp.q * g.n_stages, MB, split ? sp.m : 1)) {
+    *used = split ? MHC_SCHED_SPLIT : MHC_SCHED_TILES;
+    *n_sub = TR ? WT : 1;
+    if (sp.q > 0) {
+      GemmGeom w = g;
+      w.ipw = g.n_stages;
+      w.total_iters = (int64_t)sp.q * n_cu * g.n_stages;
+      hipError_t e = hipSuccess;
+      if (TR && WT > 1) {
+        // a whole tile's sum is the first of its part's WT, the others zero
+        w.M_pad = g.M_pad * WT;
+        e = launch_fill_i32(s, reinterpret_cast<int*>(out), (int)(g.M_pad * g.ntb * 3), 0);
+        if (e != hipSuccess) return e;
+      }
+      hipLaunchKernelGGL((k_gemm<PREC, WM, WT, MB, TR>), dim3((unsigned)(sp.q * n_cu)), dim3(256), 0, s, ws, w);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
     }
+    const ChanTiles ct{(int64_t)sp.q * n_cu, WM * MB, WT};
+    return split ? launch_chan<PREC, TR, 1>(s, g, sp, ct, rest, n_cu) : launch_chan<PREC, TR, 0>(s, g, sp, ct, rest, n_cu);
+  }
+  if (split) {
+    sp.cnt = tile_cnt;
+    hipLaunchKernelGGL((k_gemm_split<PREC, WM, WT, MB, TR>), dim3((unsigned)n_cu), dim3(256), 0, s, ws, g, sp);
+    *used = MHC_SCHED_SPLIT;
+    return hipGetLastError();
   }
   int64_t G = n_tiles;
   g.ipw = g.n_stages;
@@ -913,7 +1207,7 @@ template <int PREC>
 static hipError_t launch_gemm_prec(hipStream_t s, const void* E, const void* B, int64_t M_pad, int64_t K_pad, int ntb,
                                    float* out, int layout_g, int* n_parts, float* ws, int64_t ws_floats,
                                    int* tile_cnt, int n_cu, int sched, const float* row_scale,
-                                   const float* col_scale, int* used) {
+                                   const float* col_scale, int* used, int* n_sub) {
   GemmGeom g{};
   g.K_pad = K_pad;
   g.M_pad = M_pad;
@@ -927,9 +1221,9 @@ static hipError_t launch_gemm_prec(hipStream_t s, const void* E, const void* B, 
   // slot-major one
 #define MHC_SHAPE(WM, WT, MB, ROWS)                                                                              \
   (layout_g ? launch_gemm_shape<PREC, WM, WT, MB, false>(s, E, B, out, ws, ws_floats, tile_cnt, g,               \
-                                                         (int)(M_pad / (ROWS)), n_cu, sched, used)              \
+                                                         (int)(M_pad / (ROWS)), n_cu, sched, used, n_sub)       \
             : launch_gemm_shape<PREC, WM, WT, MB, true>(s, E, B, out, ws, ws_floats, tile_cnt, g,                \
-                                                        (int)(M_pad / (ROWS)), n_cu, sched, used))
+                                                        (int)(M_pad / (ROWS)), n_cu, sched, used, n_sub))
   if (ntb % 4 == 0) {
     // 128 slots x 4 t-blocks per tile
     g.n_ntiles = ntb / 4;
@@ -949,10 +1243,11 @@ static hipError_t launch_gemm_prec(hipStream_t s, const void* E, const void* B, 
 hipError_t launch_gemm(hipStream_t s, int prec, const void* E, const void* B, int64_t M_pad, int64_t K_pad,
                        int ntb, float* out, int layout_g, int* n_parts, float* ws, int64_t ws_floats,
                        int* tile_cnt, int n_cu, int sched, const float* row_scale, const float* col_scale,
-                       int* used) {
+                       int* used, int* n_sub) {
+  *n_sub = 1;
 #define MHC_GEMM(P) \
   launch_gemm_prec<P>(s, E, B, M_pad, K_pad, ntb, out, layout_g, n_parts, ws, ws_floats, tile_cnt, n_cu, sched, \
-                      row_scale, col_scale, used)
+                      row_scale, col_scale, used, n_sub)
   switch (prec) {
     case PREC_BF16X3: return MHC_GEMM(PREC_BF16X3);
     case PREC_FP8: return MHC_GEMM(PREC_FP8);
@@ -964,7 +1259,7 @@ hipError_t launch_gemm(hipStream_t s, int prec, const void* E, const void* B, in
 
 template <int PREC, int WM, int WT, int MB, bool TR>
 static hipError_t launch_dir_shape(hipStream_t s, GemmGeom g, int s3, int64_t region, float* ws, int64_t ws_floats,
-                                   int n_cu) {
+                                   int n_cu, int* n_sub) {
   constexpr int NBR = MB * 3 * 16;
   const int64_t n_tiles = (g.M_pad / (WM * MB * 32)) * g.n_ntiles;
   const int64_t G = std::min<int64_t>({n_tiles, (int64_t)n_cu, ws_floats / ((int64_t)2 * NBR * 256)});
@@ -972,6 +1267,11 @@ static hipError_t launch_dir_shape(hipStream_t s, GemmGeom g, int s3, int64_t re
   g.s3 = s3;
   g.region = region;
   g.ws = ws;
+  const int64_t units = n_tiles * WM * MB * WT;
+  if (chan_us(PREC, units, g.n_stages, n_cu) < tile_us(PREC, (double)((n_tiles + G - 1) / G) * g.n_stages, MB, 1)) {
+    *n_sub = TR ? WT : 1;
+    return launch_chan<PREC, TR, 2>(s, g, SplitPlan{}, ChanTiles{0, WM * MB, WT}, n_tiles, n_cu);
+  }
   hipLaunchKernelGGL((k_gemm_dir<PREC, WM, WT, MB, TR>), dim3((unsigned)G), dim3(256), 0, s, g);
   return hipGetLastError();
 }
@@ -979,7 +1279,8 @@ static hipError_t launch_dir_shape(hipStream_t s, GemmGeom g, int s3, int64_t re
 template <int PREC>
 static hipError_t launch_gemm_dir_prec(hipStream_t s, const void* E, const void* B, int64_t M_pad, int64_t n3, int ntb,
                                        float* out, int64_t region, int layout_g, int* n_parts, float* ws,
-                                       int64_t ws_floats, int n_cu, const float* row_scale, const float* col_scale) {
+                                       int64_t ws_floats, int n_cu, const float* row_scale, const float* col_scale,
+                                       int* n_sub) {
   constexpr int SD = stage_dofs(PREC);
   if (n3 % SD != 0) return hipErrorInvalidValue;
   GemmGeom g{};
@@ -995,8 +1296,8 @@ static hipError_t launch_gemm_dir_prec(hipStream_t s, const void* E, const void*
   g.col_scale = col_scale;
   const int s3 = (int)(n3 / SD);
 #define MHC_DSHAPE(WM, WT, MB)                                                                           \
-  (layout_g ? launch_dir_shape<PREC, WM, WT, MB, false>(s, g, s3, region, ws, ws_floats, n_cu)            \
-            : launch_dir_shape<PREC, WM, WT, MB, true>(s, g, s3, region, ws, ws_floats, n_cu))
+  (layout_g ? launch_dir_shape<PREC, WM, WT, MB, false>(s, g, s3, region, ws, ws_floats, n_cu, n_sub)     \
+            : launch_dir_shape<PREC, WM, WT, MB, true>(s, g, s3, region, ws, ws_floats, n_cu, n_sub))
   if (ntb % 4 == 0) {
     g.n_ntiles = ntb / 4;
     *n_parts = g.n_ntiles;
@@ -1014,11 +1315,12 @@ static hipError_t launch_gemm_dir_prec(hipStream_t s, const void* E, const void*
 
 hipError_t launch_gemm_dir(hipStream_t s, int prec, const void* E, const void* B, int64_t M_pad, int64_t n3, int ntb,
                            float* out, int64_t region, int layout_g, int* n_parts, float* ws, int64_t ws_floats,
-                           int n_cu, const float* row_scale, const float* col_scale) {
+                           int n_cu, const float* row_scale, const float* col_scale, int* n_sub) {
   if (n3 <= 0) return hipErrorInvalidValue;
+  *n_sub = 1;
 #define MHC_DIRP(P) \
   launch_gemm_dir_prec<P>(s, E, B, M_pad, n3, ntb, out, region, layout_g, n_parts, ws, ws_floats, n_cu, row_scale, \
-                          col_scale)
+                          col_scale, n_sub)
   switch (prec) {
     case PREC_BF16X3: return MHC_DIRP(PREC_BF16X3);
     case PREC_FP8: return MHC_DIRP(PREC_FP8);

@@ -818,7 +818,7 @@ static void fold_step(mhc_ctx* ctx, int t_count, int64_t* xoff, int64_t* tbuf) {
 // With the motion-direction split, pass dir in {0, 1, 2} accumulates into its
 // own slice of the bin sums and correlation sums; the whole Eq. 10 total is
 // summed in pass 0 only (every pass rewrites the same GKMA history entries).
-static mhc_status block_back(mhc_ctx* ctx, int t_count, int n_parts, const int64_t* t0_dev, int dir = -1,
+static mhc_status block_back(mhc_ctx* ctx, int t_count, int n_parts, int n_sub, const int64_t* t0_dev, int dir = -1,
                              const int64_t* xoff_dev = nullptr, const int64_t* tbuf_dev = nullptr) {
   const auto& c = ctx->cfg;
   const bool gk = c.methods & MHC_GKMA;
@@ -836,6 +836,7 @@ static mhc_status block_back(mhc_ctx* ctx, int t_count, int n_parts, const int64
   a.in = ctx->dJ + (one ? d * ctx->j_region : 0);
   a.layout_g = gk ? 1 : 0;
   a.n_parts = n_parts;
+  a.n_sub = n_sub;
   a.M_pad = ctx->M_pad;
   a.ld = ld;
   a.t_count = t_count;
@@ -933,15 +934,15 @@ static mhc_status run_block(mhc_ctx* ctx, const float* v, const float* W, int t_
     if ((st = block_front(ctx, v, W, t_count))) return st;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed && (st = timing_begin(ctx, &e0, &e1))) return st;
-    int n_parts = 0;
+    int n_parts = 0, n_sub = 1;
     HIP_TRY(launch_gemm_dir(ctx->stream, c.precision, ctx->dE, ctx->dB, ctx->M_pad, ctx->n3, ctx->t_pad / 32, ctx->dJ,
                             ctx->j_region, gk ? 1 : 0, &n_parts, wk.ws, wk.ws_floats, ctx->n_cu, ctx->d_rowscale,
-                            ctx->d_colscale),
+                            ctx->d_colscale, &n_sub),
             "direction-split contraction");
     ctx->last_sched = MHC_SCHED_TILES;
     if (e1) HIP_TRY(hipEventRecord(e1, ctx->stream), "event record");
     for (int d = 0; d < 3; ++d)
-      if ((st = block_back(ctx, t_count, n_parts, nullptr, d))) return st;
+      if ((st = block_back(ctx, t_count, n_parts, n_sub, nullptr, d))) return st;
     ctx->n_samples += t_count;
     ctx->last_block = t_count;
     return MHC_OK;
@@ -951,7 +952,7 @@ static mhc_status run_block(mhc_ctx* ctx, const float* v, const float* W, int t_
     if ((st = block_front(ctx, v, W, t_count, nullptr, dir))) return st;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed && (st = timing_begin(ctx, &e0, &e1))) return st;
-    int n_parts = 0;
+    int n_parts = 0, n_sub = 1;
     if (c.t_block == 1) {
       HIP_TRY(launch_gemv_f32(ctx->stream, reinterpret_cast<const float*>(ctx->dE),
                               reinterpret_cast<const float*>(ctx->dB), t_count, ctx->M_pad, ctx->K_pad, ctx->dJ,
@@ -961,11 +962,11 @@ static mhc_status run_block(mhc_ctx* ctx, const float* v, const float* W, int t_
     } else {
       HIP_TRY(launch_gemm(ctx->stream, c.precision, ctx->dE, ctx->dB, ctx->M_pad, ctx->K_pad, ctx->t_pad / 32,
                           ctx->dJ, gk ? 1 : 0, &n_parts, wk.ws, wk.ws_floats, wk.cnt, ctx->n_cu, c.schedule,
-                          ctx->d_rowscale, ctx->d_colscale, &ctx->last_sched),
+                          ctx->d_rowscale, ctx->d_colscale, &ctx->last_sched, &n_sub),
               "batched contraction");
     }
     if (e1) HIP_TRY(hipEventRecord(e1, ctx->stream), "event record");
-    if ((st = block_back(ctx, t_count, n_parts, nullptr, dir))) return st;
+    if ((st = block_back(ctx, t_count, n_parts, n_sub, nullptr, dir))) return st;
   }
   ctx->n_samples += t_count;
   ctx->last_block = t_count;
@@ -1582,6 +1583,7 @@ mhc_status build_back(mhc_group* g) {
     a.in = c->dJ;
     a.layout_g = gk ? 1 : 0;
     a.n_parts = g->n_parts[i];
+    a.n_sub = 1;
     a.M_pad = c->M_pad;
     a.ld = c->t_pad;
     a.t_count = T;
@@ -1736,9 +1738,9 @@ mhc_status group_block(mhc_group* g, bool timed) {
     const int64_t* w = reinterpret_cast<const int64_t*>(g->d_tab + TAB_W * i);
     mhc_status s2 = MHC_OK;
     if (c->n_dir > 1) {   // the three directions' regions, one after the other
-      for (int d = 0; d < 3 && !s2; ++d) s2 = block_back(c, g->t_block, g->n_parts[i], w + 2, d, w + 3, w + 4);
+      for (int d = 0; d < 3 && !s2; ++d) s2 = block_back(c, g->t_block, g->n_parts[i], 1, w + 2, d, w + 3, w + 4);
     } else {
-      s2 = block_back(c, g->t_block, g->n_parts[i], w + 2, -1, w + 3, w + 4);
+      s2 = block_back(c, g->t_block, g->n_parts[i], 1, w + 2, -1, w + 3, w + 4);
     }
     return s2 ? gfail(g, s2, c->err) : MHC_OK;
   });

@@ -137,11 +137,14 @@ hipError_t launch_fill_i32(hipStream_t s, int* p, int n, int v);
 //   gkma :  out[3][M_pad][t_pad]
 //   ws      stream-K workspace (ws_floats floats); n_cu = compute units
 //   sched   0 = automatic, 1 = one tile per work-group, 2 = stream-K
-// Returns the number of column tiles through *n_parts.
+// Returns the number of column tiles through *n_parts, and through *n_sub the
+// number of float32 sums each hnema part is written as: out[ntile][n_sub]
+// [M_pad][3], one per t-block where the t-blocks of a tile ran apart (the
+// reduction adds them in order, as the tile's epilogue would), else 1.
 hipError_t launch_gemm(hipStream_t s, int prec, const void* E, const void* B, int64_t M_pad,
                        int64_t K_pad, int ntb, float* out, int layout_g, int* n_parts, float* ws,
                        int64_t ws_floats, int* tile_cnt, int n_cu, int sched, const float* row_scale,
-                       const float* col_scale, int* used);
+                       const float* col_scale, int* used, int* n_sub);
 
 // Motion-direction split as one contraction: K ordered direction-major
 // (third nu = dofs (i, nu) at k = nu*n3 + i, n3 a multiple of the precision's
@@ -149,16 +152,17 @@ hipError_t launch_gemm(hipStream_t s, int prec, const void* E, const void* B, in
 // nu at out + nu * region), each laid out as launch_gemm's out.  ws holds two
 // bracket slots per work-group (ws_floats floats); n_cu = compute units;
 // row_scale / col_scale as for launch_gemm (e4m3; whole-column activation
-// scales, the same for every third).
+// scales, the same for every third); n_sub as for launch_gemm.
 hipError_t launch_gemm_dir(hipStream_t s, int prec, const void* E, const void* B, int64_t M_pad, int64_t n3, int ntb,
                            float* out, int64_t region, int layout_g, int* n_parts, float* ws, int64_t ws_floats,
-                           int n_cu, const float* row_scale, const float* col_scale);
+                           int n_cu, const float* row_scale, const float* col_scale, int* n_sub);
 
 // dofs per k-stage of a precision's T-batched contraction.
 int stage_dofs_of(int prec);
 
 // Bin reduction + float64 accumulation.
-//   HNEMA-only: part sums in[n_parts][M_pad][3] -> hsum/hcomp[nb][3] (Neumaier)
+//   HNEMA-only: part sums in[n_parts][n_sub][M_pad][3] -> hsum/hcomp[nb][3] (Neumaier);
+//               the n_sub float32 sums of a part are added in float32 first
 //   GKMA:       per-step in[3][M_pad][ld]      -> X[(b*3+mu)][ld] float64, and
 //               (if hsum) the HNEMA sums of the same steps.
 //   The last work-group distributes the per-step totals jtot[t][3]:
@@ -169,7 +173,7 @@ int stage_dofs_of(int prec);
 // rows in order.  slot_bin[slot] is the bin of a slot (-1: padding).
 constexpr int REDUCE_SEG = 64;
 struct ReduceArgs {
-  const float* in; int layout_g; int n_parts; int64_t M_pad; int64_t ld; int t_count;
+  const float* in; int layout_g; int n_parts; int n_sub; int64_t M_pad; int64_t ld; int t_count;
   const int32_t* bin_off; int nb;
   const int32_t* slot_bin; double* seg_part; int n_seg;      // GKMA segment pass
   const double* jtot;
