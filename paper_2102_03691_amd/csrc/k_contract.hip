@@ -154,11 +154,132 @@ k_gemv_f32(const f32x4* __restrict__ E, const float* __restrict__ B, int n_steps
   }
 }
 
+// Several steps of the per-step path at once.  Streaming E once per step is
+// all HBM (604 MB per step at 12288 modes); the steps of one push are known
+// together, so here a work-group takes GEMV_TS steps of 32 slots: each of its
+// waves holds 8 rows of E in registers and uses them for the four steps,
+// whose activations all four waves read from LDS.  The step groups of the
+// same rows are neighbours (one XCD) and find the rows in its L2.  Bound:
+// FP32 vector FMA issue (512 of about 560 instructions per 256 dofs).  Every
+// sum has the terms and the order of k_gemv_f32, so its bits: a lane's
+// partial over its dofs, then the butterfly over the lanes, here for two
+// accumulators per exchange (each half-wave keeps one and sends the other;
+// a + b = b + a).  Measured, 4096 atoms, 64 steps: 5696 -> 1190 us.
+constexpr int GEMV_TS = 4;
+constexpr int64_t GEMV_STEPS_MIN_UNITS = 1024;   // 256 CUs x 4 SIMDs
+
+__global__ void __launch_bounds__(256, 2)
+k_gemv_steps(const f32x4* __restrict__ E, const float* __restrict__ B, int n_steps, int64_t M_pad, int64_t K_pad,
+             float* __restrict__ out, int layout_g, int64_t ld) {
+  constexpr int R = GEMV_ROWS, TS = GEMV_TS;
+  static_assert(R == 8 && TS == 4, "the exchange below leaves two of the 128 sums in each lane");
+  __shared__ f32x4 lds[2][TS][4][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int n_sg = (n_steps + TS - 1) / TS;
+  const int lin = (gridDim.x % 8 == 0) ? (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
+  const int t0 = lin % n_sg * TS;
+  const int64_t row0 = ((int64_t)(lin / n_sg) * 4 + wave) * R;
+  const int64_t KC = K_pad >> 2;
+  const gf32x4* Er = (const gf32x4*)E + row0 * KC;
+  // wave w stages step t0 + w (the last step again past the end: not stored)
+  const gf32x4* Bt = (const gf32x4*)B + (int64_t)min(t0 + wave, n_steps - 1) * 4 * KC;
+  const int n_it = (int)(KC / 64);                      // even: K_pad is a multiple of 512
+  float acc[TS * R * 4];                                // [step][row][channel]
+#pragma unroll
+  for (int i = 0; i < TS * R * 4; ++i) acc[i] = 0.f;
+  f32x4 ea[R], eb[R], st[4];
+  auto load_E = [&](f32x4 (&e)[R], int it) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) e[r] = (Er + (r * KC + (int64_t)it * 64))[lane];
+  };
+  auto load_B = [&](int it) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) st[c] = (Bt + (c * KC + (int64_t)it * 64))[lane];
+  };
+  auto store_B = [&](int buf) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) lds[buf][wave][c][lane] = st[c];
+  };
+  auto consume = [&](const f32x4 (&e)[R], int buf) {
+#pragma unroll
+    for (int s = 0; s < TS; ++s) {
+      f32x4 b[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) b[c] = lds[buf][s][c][lane];
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          float a = acc[(s * R + r) * 4 + c];
+          a = fmaf(e[r].x, b[c].x, a);
+          a = fmaf(e[r].y, b[c].y, a);
+          a = fmaf(e[r].z, b[c].z, a);
+          a = fmaf(e[r].w, b[c].w, a);
+          acc[(s * R + r) * 4 + c] = a;
+        }
+    }
+  };
+  load_B(0);
+  load_E(ea, 0);
+  store_B(0);
+  __syncthreads();
+  for (int it = 0; it < n_it; it += 2) {
+    load_B(it + 1);
+    load_E(eb, it + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    consume(ea, 0);
+    store_B(1);
+    __syncthreads();
+    load_B(min(it + 2, n_it - 1));
+    load_E(ea, min(it + 2, n_it - 1));
+    __builtin_amdgcn_sched_barrier(0);
+    consume(eb, 1);
+    store_B(0);
+    __syncthreads();
+  }
+  // after the exchange over lane bit `off` a lane keeps the lower or the upper
+  // half of the sums: lane l ends with sums 2 l and 2 l + 1
+#pragma unroll
+  for (int off = 32, n = TS * R * 2; off > 0; off >>= 1, n >>= 1) {
+    const bool up = (lane & off) != 0;
+#pragma unroll
+    for (int i = 0; i < TS * R * 2; ++i) {
+      if (i >= n) break;
+      const float keep = up ? acc[i + n] : acc[i], send = up ? acc[i] : acc[i + n];
+      acc[i] = keep + __shfl_xor(send, off);
+    }
+  }
+  const float x = __shfl(acc[0], lane & ~1);            // channel 0 of this (row, step)
+  const int64_t slot = row0 + (lane >> 1) % R;
+  const int t = t0 + (lane >> 1) / R;
+  if (t >= n_steps) return;
+  const int64_t ms = layout_g ? M_pad * ld : 1;         // mu stride
+  float* o = layout_g ? out + slot * ld + t : out + ((int64_t)t * M_pad + slot) * 3;
+  if (lane & 1) {
+    o[ms] = x * acc[0];
+    o[2 * ms] = x * acc[1];
+  } else {
+    o[0] = x * acc[1];
+  }
+}
+
 hipError_t launch_gemv_f32(hipStream_t s, const float* E, const float* B, int n_steps, int64_t M_pad,
                            int64_t K_pad, float* out, int layout_g, int64_t ld) {
   if (n_steps <= 0) return hipSuccess;
-  if (M_pad % GEMV_ROWS != 0 || K_pad % K_ALIGN_GEMV != 0) return hipErrorInvalidValue;
+  if (M_pad % M_ALIGN != 0 || K_pad % K_ALIGN_GEMV != 0) return hipErrorInvalidValue;
   const int64_t units = (M_pad / GEMV_ROWS) * n_steps;
+  // One pass over E for up to four steps, where the waves of one step each
+  // would be more than one per SIMD: below that E is read by idle CUs anyway
+  // and the longer waves are slower (1000 atoms: 2 steps 18.0 -> 25.5 us, 3
+  // steps 27.2 -> 25.2 us, 16 steps 64 -> 32 us).
+  if (units > GEMV_STEPS_MIN_UNITS && n_steps >= 2) {
+    const int64_t wgs = (M_pad / (4 * GEMV_ROWS)) * ((n_steps + GEMV_TS - 1) / GEMV_TS);
+    if (wgs > INT32_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_gemv_steps, dim3((unsigned)wgs), dim3(256), 0, s, reinterpret_cast<const f32x4*>(E), B,
+                       n_steps, M_pad, K_pad, out, layout_g, ld);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_gemv_f32, dim3((unsigned)((units + 3) / 4)), dim3(256), 0, s,
                      reinterpret_cast<const f32x4*>(E), B, n_steps, M_pad, K_pad, out, layout_g, ld);
   return hipGetLastError();

@@ -114,6 +114,7 @@ struct mhc_ctx {
   int32_t* d_slot_bin = nullptr;  // GKMA: bin of each slot (-1: padding)
   double* d_seg_part = nullptr;   // GKMA: segment rows of the bin reduction
   int n_seg = 0;
+  double* d_slotsum = nullptr;    // per-step HNEMA: sums over a push's steps [M_pad][3]
   float* d_rowscale = nullptr;  // e4m3: per-slot scale of E
   float* d_colscale = nullptr;  // e4m3: per-(channel, step) scale of the activations
   float* d_colpart = nullptr;   // e4m3: per-atom-chunk maxima behind d_colscale
@@ -603,6 +604,11 @@ static mhc_status finalize_impl(mhc_ctx* ctx) {
   if ((st = dev_alloc(ctx, (size_t)N * 4, &psm, "sqrt m"))) return st;
   if ((st = dev_alloc(ctx, (size_t)N * 4, &pism, "1/sqrt m"))) return st;
   if ((st = dev_alloc(ctx, (size_t)(nb + 1) * 4, &poff, "bin offsets"))) return st;
+  if (c.t_block == 1 && !gk) {
+    void* pss = nullptr;
+    if ((st = dev_alloc(ctx, (size_t)M_pad * 3 * 8, &pss, "slot sums"))) return st;
+    ctx->d_slotsum = reinterpret_cast<double*>(pss);
+  }
   if (c.precision == MHC_PREC_FP8 || c.precision == MHC_PREC_FP8X3) {
     void* pcs = nullptr;
     if ((st = dev_alloc(ctx, (size_t)4 * t_pad * 4, &pcs, "column scales"))) return st;
@@ -837,6 +843,10 @@ static mhc_status block_back(mhc_ctx* ctx, int t_count, int n_parts, int n_sub, 
   a.layout_g = gk ? 1 : 0;
   a.n_parts = n_parts;
   a.n_sub = n_sub;
+  // the sum over steps apart from the sum over slots where a bin's work-group
+  // would otherwise add more than 16 values per thread one after another
+  const int64_t rounds = n_parts * (1 + 3 * ctx->M_used / ctx->nb / 256);
+  a.slot_sum = rounds > 16 ? ctx->d_slotsum : nullptr;
   a.M_pad = ctx->M_pad;
   a.ld = ld;
   a.t_count = t_count;

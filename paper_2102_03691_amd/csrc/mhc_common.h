@@ -186,6 +186,7 @@ struct ReduceArgs {
   int64_t ldx;              // leading dimension of X (>= ld: X keeps several blocks)
   int64_t xoff;             // column of X where this block's first step goes
   const int64_t* xoff_dev;  // if set, xoff is read here (the group's block table)
+  double* slot_sum;         // HNEMA-only, n_sub = 1: if set, the parts are first summed per (slot, mu) into it [M_pad][3]
 };
 hipError_t launch_reduce(hipStream_t s, const ReduceArgs& a);
 
