@@ -16,20 +16,25 @@ struct CellGrid {
 };
 
 // Device buffers of the neighbour lists: nbr, rev [max_nb][N] (slot-major),
-// n_nb [N]; cell_of [N], atoms [N]; count, fill [n_cells], start [n_cells + 1];
-// tile_sums [ceil(n_cells / 1024)] (scan workspace); flags[0] = largest
-// neighbour count found, flags[1] = 1 if a reverse slot was missing,
-// flags[2] = largest count inside the bond lists' cutoff.
+// n_nb [N]; cell_of, place [N] (an atom's cell and its place in it); atoms [N]
+// and cpos [N][3] (the atoms by cell and their positions); count [n_cells]
+// (zero between searches), start [n_cells + 1]; tile_sums [ceil(n_cells / 1024)]
+// (scan workspace); most [ceil(N / 16)] (largest counts of the search's
+// work-groups); flags[0] = largest neighbour count found, flags[1] = 1 if a
+// reverse slot was missing, flags[2] = largest count inside the bond lists'
+// cutoff.
 struct NeighborBufs {
   int* nbr;
   int* rev;
   int* n_nb;
   int* cell_of;
+  int* place;
   int* atoms;
+  double* cpos;
   int* count;
-  int* fill;
   int* start;
   int* tile_sums;
+  int2* most;
   int* flags;
 };
 

@@ -42,6 +42,7 @@ struct mhc_virial {
   bool lists_ok = false;
 
   std::vector<void*> allocs;
+  void* h_read = nullptr;   // 64 bytes of pinned memory that flags and the thermostat are read back into
   double* d_mass = nullptr;
   NeighborBufs nb{};
   double *d_dd = nullptr, *d_U = nullptr;
@@ -127,6 +128,8 @@ mhc_status venter(mhc_virial* v) {
 void vfree(mhc_virial* v) {
   for (void* p : v->allocs) (void)hipFree(p);
   v->allocs.clear();
+  if (v->h_read) (void)hipHostFree(v->h_read);
+  v->h_read = nullptr;
 }
 
 template <class T>
@@ -243,18 +246,24 @@ mhc_status mhc_virial_create(int device, void* hip_stream, int64_t n_atoms, cons
   const int64_t n_cells = (int64_t)v->cg.nc[0] * v->cg.nc[1] * v->cg.nc[2];
   NeighborBufs& b = v->nb;
   bool ok = valloc(v, N, &v->d_mass) && valloc(v, MN, &b.nbr) && valloc(v, MN, &b.rev) && valloc(v, N, &b.n_nb) &&
-            valloc(v, N, &b.cell_of) && valloc(v, N, &b.atoms) && valloc(v, n_cells, &b.count) &&
-            valloc(v, n_cells, &b.fill) && valloc(v, n_cells + 1, &b.start) &&
-            valloc(v, (n_cells + 1023) / 1024, &b.tile_sums) && valloc(v, 3, &b.flags) &&
+            valloc(v, N, &b.cell_of) && valloc(v, N, &b.place) && valloc(v, N, &b.atoms) &&
+            valloc(v, 3 * N, &b.cpos) && valloc(v, n_cells, &b.count) && valloc(v, n_cells + 1, &b.start) &&
+            valloc(v, (n_cells + 1023) / 1024, &b.tile_sums) && valloc(v, (N + 15) / 16, &b.most) && valloc(v, 3, &b.flags) &&
             valloc(v, 3 * MN, &v->d_dd) && valloc(v, N, &v->d_U) && valloc(v, 3 * N, &v->d_F) &&
             valloc(v, 4, &v->d_thermo) &&
             valloc(v, std::max(md_nvt_parts(N), gather_blocks(N, 64)), &v->d_kepart) &&
             valloc(v, MN, &v->bb.nbr) && valloc(v, MN, &v->bb.rev) && valloc(v, N, &v->bb.n_nb) &&
             valloc(v, N, &v->bb.mask) && valloc(v, 3 * N, &v->bb.ref) && valloc(v, 12, &v->bb.flags);
   if (!ok) return cleanup(MHC_ERR_OOM, "device allocation failed");
+  if (hipHostMalloc(reinterpret_cast<void**>(&v->h_read), 64) != hipSuccess) {
+    (void)hipGetLastError();
+    v->h_read = nullptr;
+    return cleanup(MHC_ERR_OOM, "pinned allocation failed");
+  }
   v->bb.need = v->bb.flags + 8;
   v->bond_skin = std::min(rc - (p.R + p.D), 0.5);
-  if (hipMemcpyAsync(v->d_mass, mass_amu, N * sizeof(double), hipMemcpyHostToDevice, v->stream) != hipSuccess ||
+  if (launch_zero_i32(v->stream, b.count, (int)n_cells) != hipSuccess ||
+      hipMemcpyAsync(v->d_mass, mass_amu, N * sizeof(double), hipMemcpyHostToDevice, v->stream) != hipSuccess ||
       hipStreamSynchronize(v->stream) != hipSuccess)
     return cleanup(MHC_ERR_HIP, "copy of the masses failed");
   *out = v;
@@ -285,8 +294,8 @@ mhc_status mhc_virial_neighbors(mhc_virial* v, const double* pos, int32_t* max_f
   v->lists_ok = false;
   VHIP_TRY(launch_neighbors(v->stream, pos, v->N, v->cg, v->rc, v->tp.R + v->tp.D + v->bond_skin, v->max_nb, v->nb),
            "neighbour search");
-  int flags[3] = {0, 0, 0};
-  VHIP_TRY(hipMemcpyAsync(flags, v->nb.flags, sizeof(flags), hipMemcpyDeviceToHost, v->stream), "read flags");
+  const int* flags = static_cast<const int*>(v->h_read);
+  VHIP_TRY(hipMemcpyAsync(v->h_read, v->nb.flags, 3 * sizeof(int), hipMemcpyDeviceToHost, v->stream), "read flags");
   VHIP_TRY(hipStreamSynchronize(v->stream), "neighbour search sync");
   if (max_found) *max_found = flags[0];
   if (flags[0] > v->max_nb)
@@ -507,8 +516,8 @@ mhc_status md_run(mhc_virial* v, double* pos, double* vel, double dt, int32_t n_
   }
   if (F) VHIP_TRY(hipMemcpyAsync(F, v->d_F, (size_t)N * 3 * 8, hipMemcpyDeviceToDevice, v->stream), "copy forces");
   if (any_compact) {
-    int f[3] = {0, 0, 0};
-    VHIP_TRY(hipMemcpyAsync(f, v->bb.flags, sizeof(f), hipMemcpyDeviceToHost, v->stream), "read bond flags");
+    const int* f = static_cast<const int*>(v->h_read);
+    VHIP_TRY(hipMemcpyAsync(v->h_read, v->bb.flags, 3 * sizeof(int), hipMemcpyDeviceToHost, v->stream), "read bond flags");
     VHIP_TRY(hipStreamSynchronize(v->stream), "md sync");
     if (f[1])
       return vfail(v, MHC_ERR_INVALID_ARG,
@@ -518,8 +527,8 @@ mhc_status md_run(mhc_virial* v, double* pos, double* vel, double dt, int32_t n_
     if (f[2]) return vfail(v, MHC_ERR_INVALID_ARG, "bond lists are not symmetric (non-finite positions?)");
   }
   if (nvt) {
-    double th[4] = {0.0, 0.0, 0.0, 0.0};
-    VHIP_TRY(hipMemcpyAsync(th, v->d_thermo, sizeof(th), hipMemcpyDeviceToHost, v->stream), "read thermostat");
+    const double* th = static_cast<const double*>(v->h_read);
+    VHIP_TRY(hipMemcpyAsync(v->h_read, v->d_thermo, 4 * sizeof(double), hipMemcpyDeviceToHost, v->stream), "read thermostat");
     VHIP_TRY(hipStreamSynchronize(v->stream), "md sync");
     nvt->state[0] = th[0];
     nvt->state[1] = th[1];
