@@ -606,16 +606,15 @@ __global__ void __launch_bounds__(SITE_WG) k_tersoff_site(TersoffArgs a, Tersoff
     for (int q = 0; q < n; ++q) acc += sh[7][gb + q];
     a.U[i] = 0.5 * acc;
   }
-  const int64_t mn = (int64_t)a.max_nb * N;
 #pragma unroll
   for (int k = 0; k < SPL; ++k) {
     const int s = s0 + k * LPA;
     if (s >= n) continue;
-    const int64_t es = (int64_t)s * N + i;
+    double* dd = a.dd + 3 * ((int64_t)s * N + i);
     if (fc[k] == 0.0) {
-      a.dd[es] = 0.0;
-      a.dd[mn + es] = 0.0;
-      a.dd[2 * mn + es] = 0.0;
+      dd[0] = 0.0;
+      dd[1] = 0.0;
+      dd[2] = 0.0;
       continue;
     }
     // dU_i/dr_ij for this slot's pair j
@@ -652,114 +651,134 @@ __global__ void __launch_bounds__(SITE_WG) k_tersoff_site(TersoffArgs a, Tersoff
       ky = fma(ka, cy, fma(kb, uy, ky));
       kz = fma(ka, cz, fma(kb, uz, kz));
     }
-    a.dd[es] = radial * ux - 0.5 * (adb[k] * zx + kx);
-    a.dd[mn + es] = radial * uy - 0.5 * (adb[k] * zy + ky);
-    a.dd[2 * mn + es] = radial * uz - 0.5 * (adb[k] * zz + kz);
+    dd[0] = radial * ux - 0.5 * (adb[k] * zx + kx);
+    dd[1] = radial * uy - 0.5 * (adb[k] * zy + ky);
+    dd[2] = radial * uz - 0.5 * (adb[k] * zz + kz);
   }
 }
 
-// Atom i's sums over its pairs (the pair terms of its LPA lanes in sh, slot
-// order) and every output of the gather kernel; with o.kick_vel, also the
-// second half kick and thermostat scale of the step on its velocity (after
-// E_i has read it) and the float32 copy.  Returns m_i |v_i|^2 after the kick
-// (0 without one).
-__device__ __forceinline__ double gather_atom(const TersoffArgs& a, const GatherArgs& o, const double (*sh)[256],
-                                              int g0, int n, int64_t i) {
-  double t[12];
-#pragma unroll
-  for (int q = 0; q < 12; ++q) t[q] = 0.0;
-  for (int k = 0; k < n; ++k)
-#pragma unroll
-    for (int q = 0; q < 12; ++q) t[q] += sh[q][g0 + k];
-  const double* w = t + 3;
-  double fx[3] = {0.0, 0.0, 0.0};
-  if (o.Fext || o.add_ext) {
-    double e = a.U[i];
-    if (o.vel) {
-      const double vx = o.vel[3 * i], vy = o.vel[3 * i + 1], vz = o.vel[3 * i + 2];
-      e += 0.5 * o.mass[i] * (vx * vx + vy * vy + vz * vz) * o.ke_unit;
-    }
-#pragma unroll
-    for (int nu = 0; nu < 3; ++nu)
-      fx[nu] = e * o.fe[nu] + (o.fe[0] * w[nu] + o.fe[1] * w[3 + nu] + o.fe[2] * w[6 + nu]);
-  }
-  double f[3];
-#pragma unroll
-  for (int mu = 0; mu < 3; ++mu) f[mu] = o.add_ext ? t[mu] + fx[mu] : t[mu];
-  if (o.F)
-    for (int mu = 0; mu < 3; ++mu) o.F[3 * i + mu] = f[mu];
-  if (o.W)
-    for (int q = 0; q < 9; ++q) o.W[9 * i + q] = w[q];
-  if (o.W32)
-    for (int q = 0; q < 9; ++q) o.W32[9 * i + q] = (float)w[q];
-  if (o.Fext)
-    for (int nu = 0; nu < 3; ++nu) o.Fext[3 * i + nu] = fx[nu];
-  double mv2 = 0.0;
-  if (o.kick_vel) {   // end of an NVT step: v += c F / m, then v *= exp(-xi dt / 2)
-    const double m = o.mass[i];
-#pragma unroll
-    for (int mu = 0; mu < 3; ++mu) {
-      double v = o.kick_vel[3 * i + mu];
-      v = v + o.kick_c * f[mu] / m;
-      v = v * o.kick_scale[2];
-      o.kick_vel[3 * i + mu] = v;
-      if (o.kick_v32) o.kick_v32[3 * i + mu] = (float)v;
-      mv2 += m * v * v;
-    }
-  }
-  return mv2;
+// Orders a wave's own LDS traffic (its LDS operations complete in order; this
+// keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-// Per pair: dU_i/dr_ij - dU_j/dr_ji (Eq. 4) and r_ij (x) dU_j/dr_ji (Eq. 8);
-// the first lane of each atom sums its pairs in slot order and writes F_i,
-// W_i, E_i and F_ext (Eq. 12).
-template <int LPA>
-__global__ void __launch_bounds__(256) k_tersoff_gather(TersoffArgs a, GatherArgs o) {
-  __shared__ double sh[12][256];
-  const int tid = threadIdx.x;
-  const int s = tid & (LPA - 1);
-  const int g0 = tid - s;
+// Per pair dU_i/dr_ij - dU_j/dr_ji (Eq. 4) and r_ij (x) dU_j/dr_ji (Eq. 8),
+// LPA lanes per atom and SPL slots per lane as in the site kernel.  A round of
+// LPA slots goes through the wave's own part of LDS, from which each of the
+// atom's lanes adds its share of the twelve sums (F, then W row by row) in
+// slot order; rounds that no atom of the wave has are skipped.  The sums go
+// back to LDS, so that the three lanes of an atom finish one component each
+// (E_i, F_ext of Eq. 12, with o.kick_vel the second half kick and thermostat
+// scale of the step) and W leaves in whole lines.  Bound: the scattered reads
+// of the partners' partials (24 contiguous bytes each).  Measured against one
+// lane summing and storing for its atom, partials in three planes, 8 lanes
+// for 4 bonds: 216000 Si atoms in MD 24.2 -> 16.0 us, 8000 atoms 6.2 -> 4.9 us.
+constexpr int GATHER_WG = 256;
+template <int LPA, int SPL>
+__global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, GatherArgs o) {
+  constexpr int APW = 64 / LPA, APB = GATHER_WG / LPA;   // atoms per wave, per work-group
+  constexpr int QL = LPA >= 12 ? 1 : (12 + LPA - 1) / LPA;   // sums per lane
+  constexpr int ROW = 66;                                // padded: the lanes of an atom read different rows
+  __shared__ double pair[GATHER_WG / 64][12 * ROW];
+  __shared__ double tot[GATHER_WG / 64][APW * 12];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int s0 = lane & (LPA - 1), g = lane / LPA;       // slot of round 0; atom within the wave
+  double* sh = pair[wave];
+  double* tt = tot[wave];
   const int64_t N = a.N;
-  const int64_t i = ((int64_t)blockIdx.x * 256 + tid) / LPA;
+  const int64_t i0 = (int64_t)blockIdx.x * APB + (int64_t)wave * APW, i = i0 + g;
   const int n = i < N ? a.n_nb[i] : 0;
-  // the pair's list entry and reverse slot are loaded with the count, not
-  // after it (the rows below max_nb exist; entries at or past n are not used)
-  const int64_t es = (int64_t)s * N + i;
-  const bool row = i < N && s < a.max_nb;
-  const int jl = row ? a.nbr[es] : 0, rl = row ? a.rev[es] : 0;
-  double c[12];
+  // the first round's list entry and reverse slot are loaded with the count,
+  // not after it (the rows below max_nb exist; entries at or past n are not used)
+  const bool row = i < N && s0 < a.max_nb;
+  int jl = row ? a.nbr[(int64_t)s0 * N + i] : 0, rl = row ? a.rev[(int64_t)s0 * N + i] : 0;
+  double sum[QL];
 #pragma unroll
-  for (int q = 0; q < 12; ++q) c[q] = 0.0;
-  if (s < n) {
-    const int64_t mn = (int64_t)a.max_nb * N;
-    const int64_t j = jl;
-    const int64_t ej = (int64_t)rl * N + j;
-    const double r[3] = {min_image(a.pos[3 * j] - a.pos[3 * i], a.box[0], a.ibox[0]),
-                         min_image(a.pos[3 * j + 1] - a.pos[3 * i + 1], a.box[1], a.ibox[1]),
-                         min_image(a.pos[3 * j + 2] - a.pos[3 * i + 2], a.box[2], a.ibox[2])};
-    // a pair beyond R + D has zero partials both ways (written so by the site
-    // kernel): nothing to load or add
-    if (r[0] * r[0] + r[1] * r[1] + r[2] * r[2] < o.rcut2) {
-      const double dij[3] = {a.dd[es], a.dd[mn + es], a.dd[2 * mn + es]};
-      const double dji[3] = {a.dd[ej], a.dd[mn + ej], a.dd[2 * mn + ej]};
+  for (int q = 0; q < QL; ++q) sum[q] = 0.0;
 #pragma unroll
-      for (int mu = 0; mu < 3; ++mu) {
-        c[mu] = dij[mu] - dji[mu];
+  for (int k = 0; k < SPL; ++k) {
+    if (k > 0 && __ballot(n > k * LPA) == 0) break;
+    const int s = s0 + k * LPA;
+    double c[12];
 #pragma unroll
-        for (int nu = 0; nu < 3; ++nu) c[3 + 3 * mu + nu] = r[mu] * dji[nu];
+    for (int q = 0; q < 12; ++q) c[q] = 0.0;
+    if (s < n) {
+      const int64_t es = (int64_t)s * N + i;
+      if (k > 0) jl = a.nbr[es], rl = a.rev[es];
+      const int64_t j = jl;
+      const double r[3] = {min_image(a.pos[3 * j] - a.pos[3 * i], a.box[0], a.ibox[0]),
+                           min_image(a.pos[3 * j + 1] - a.pos[3 * i + 1], a.box[1], a.ibox[1]),
+                           min_image(a.pos[3 * j + 2] - a.pos[3 * i + 2], a.box[2], a.ibox[2])};
+      // a pair beyond R + D has zero partials both ways (written so by the site
+      // kernel): nothing to load or add
+      if (r[0] * r[0] + r[1] * r[1] + r[2] * r[2] < o.rcut2) {
+        const double* dij = a.dd + 3 * es;
+        const double* dji = a.dd + 3 * ((int64_t)rl * N + j);
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu) {
+          c[mu] = dij[mu] - dji[mu];
+#pragma unroll
+          for (int nu = 0; nu < 3; ++nu) c[3 + 3 * mu + nu] = r[mu] * dji[nu];
+        }
       }
     }
-  }
+    if (k > 0) wave_lds_fence();
 #pragma unroll
-  for (int q = 0; q < 12; ++q) sh[q][tid] = c[q];
-  __syncthreads();
-  const bool first = i < N && s == 0;
+    for (int q = 0; q < 12; ++q) sh[q * ROW + lane] = c[q];
+    wave_lds_fence();
+    const int m = min(n - k * LPA, LPA);
+    if (s0 * QL < 12) {
+      for (int t = 0; t < m; ++t)
+#pragma unroll
+        for (int q = 0; q < QL; ++q) sum[q] += sh[(s0 * QL + q) * ROW + g * LPA + t];
+    }
+  }
+  if (s0 * QL < 12) {
+#pragma unroll
+    for (int q = 0; q < QL; ++q) tt[g * 12 + s0 * QL + q] = sum[q];
+  }
+  wave_lds_fence();
   double mv2 = 0.0;
-  if (first) mv2 = gather_atom(a, o, sh, g0, n, i);
+  if (i < N && s0 < 3) {   // component s0 of atom i
+    const double* t = tt + g * 12;
+    double f = t[s0];
+    if (o.Fext || o.add_ext) {
+      double e = a.U[i];
+      if (o.vel) {
+        const double vx = o.vel[3 * i], vy = o.vel[3 * i + 1], vz = o.vel[3 * i + 2];
+        e += 0.5 * o.mass[i] * (vx * vx + vy * vy + vz * vz) * o.ke_unit;
+      }
+      const double fx = e * o.fe[s0] + (o.fe[0] * t[3 + s0] + o.fe[1] * t[6 + s0] + o.fe[2] * t[9 + s0]);
+      if (o.Fext) o.Fext[3 * i + s0] = fx;
+      if (o.add_ext) f += fx;
+    }
+    if (o.F) o.F[3 * i + s0] = f;
+    if (o.kick_vel) {
+      // end of an NVT step: v += c F / m, then v *= exp(-xi dt / 2).  E_i's
+      // loads of v (the wave's own atoms) are back before any f is known, so
+      // before any component is written
+      const double m = o.mass[i];
+      double v = o.kick_vel[3 * i + s0];
+      v = v + o.kick_c * f / m;
+      v = v * o.kick_scale[2];
+      o.kick_vel[3 * i + s0] = v;
+      if (o.kick_v32) o.kick_v32[3 * i + s0] = (float)v;
+      mv2 = m * v * v;
+    }
+  }
+  // W of the wave's atoms, consecutive values by consecutive lanes
+  const int64_t left = N - i0 < APW ? N - i0 : APW;
+  const int nw = left > 0 ? (int)left * 9 : 0;
+  if (o.W)
+    for (int e = lane; e < nw; e += 64) o.W[9 * i0 + e] = tt[e / 9 * 12 + 3 + e % 9];
+  if (o.W32)
+    for (int e = lane; e < nw; e += 64) o.W32[9 * i0 + e] = (float)tt[e / 9 * 12 + 3 + e % 9];
   if (o.ke_part) {   // the work-group's partial sum of m v^2 after the kick (uniform over the launch)
-    constexpr int APB = 256 / LPA;   // atoms per work-group
     __shared__ double kp[APB];
-    if (s == 0) kp[tid / LPA] = mv2;
+    const double y = __shfl(mv2, lane + 1), z = __shfl(mv2, lane + 2);
+    if (s0 == 0) kp[tid / LPA] = (mv2 + y) + z;
     __syncthreads();
     for (int w = APB / 2; w > 0; w >>= 1) {
       if (tid < w) kp[tid] += kp[tid + w];
@@ -819,15 +838,15 @@ hipError_t launch_neighbors(hipStream_t s, const double* pos, int64_t N, const C
 template <int LPA>
 static hipError_t launch_pair_kernels(hipStream_t s, const TersoffArgs& a, const TersoffParams& p, const GatherArgs& o,
                                       hipEvent_t e1) {
-  // the site kernel for 5..8 pairs: 4 lanes x 2 slots (most atoms of a
-  // crystal have 4 bonds, so most waves run one slot round)
+  // 5..8 pairs: 4 lanes x 2 slots (most atoms of a crystal have 4 bonds, so
+  // most waves run one slot round)
   constexpr int SL = LPA == 8 ? 4 : LPA, SPL = LPA / SL;
   hipLaunchKernelGGL((k_tersoff_site<SL, SPL>), dim3(blocks_of(a.N * SL, SITE_WG)), dim3(SITE_WG), 0, s, a, p);
   if (e1) {
     hipError_t e = hipEventRecord(e1, s);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_tersoff_gather<LPA>, dim3(blocks_of(a.N * LPA, 256)), dim3(256), 0, s, a, o);
+  hipLaunchKernelGGL((k_tersoff_gather<SL, SPL>), dim3(blocks_of(a.N * SL, GATHER_WG)), dim3(GATHER_WG), 0, s, a, o);
   return hipSuccess;
 }
 
@@ -1028,7 +1047,7 @@ hipError_t launch_thermostat(hipStream_t s, const double* part, int64_t n_part, 
   return hipGetLastError();
 }
 
-int64_t gather_blocks(int64_t N, int lpa) { return (int64_t)blocks_of(N * lpa, 256); }
+int64_t gather_blocks(int64_t N, int lpa) { return (int64_t)blocks_of(N * (lpa == 8 ? 4 : lpa), GATHER_WG); }
 
 hipError_t launch_md_nvt_start(hipStream_t s, double* pos, double* vel, const double* F, const double* mass, double c,
                                double dt, const double box[3], int64_t N, const double* st, const double* ref,

@@ -62,7 +62,7 @@ struct TersoffParams {
 };
 
 // Per-evaluation buffers: positions (device, [N][3]); neighbour lists; the
-// partials dd [3][max_nb][N] (dU_i/dr_ij); site energies U [N].
+// partials dd [max_nb][N][3] (dU_i/dr_ij); site energies U [N].
 struct TersoffArgs {
   const double* pos;
   int64_t N;
