@@ -52,16 +52,6 @@ __device__ __forceinline__ int cell_coord(double x, double L, int nc) {
 }
 
 // ------------------------------------------------------------- neighbour lists
-// atomicMax of v over the whole wave with one atomic per wave instead of one
-// per lane (the lanes of an atom-per-lane kernel all target one counter, and
-// 64 times fewer atomics on one address matter at 10^5..10^6 atoms).  Every
-// lane of the wave must call it.
-__device__ __forceinline__ void wave_atomic_max(int* addr, int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-  if ((threadIdx.x & 63) == 0 && v > 0) atomicMax(addr, v);
-}
-
 __global__ void k_set_i32(int* __restrict__ p, int value) {
   if (threadIdx.x == 0) *p = value;
 }
@@ -338,67 +328,6 @@ __global__ void __launch_bounds__(64 * REV_SLOTS) k_reverse(int64_t N, const int
   }
 }
 
-// Bond lists out of lists built with a skin: the listed pairs closer than rb
-// (rb2 = rb^2, rb = R + D + delta with delta the bond lists' own skin), in
-// list order (so still ascending j), at most max_b per atom.  mask[i] bit s =
-// list slot s of i is kept; count[i] = pairs kept; ref[i] = pos[i] (the
-// positions of the build, for the displacement test); flags[0] = largest
-// count found (atomic max); flags[1] = 1 if an atom had more than max_b.
-// need (null: always build) = the rebuild flag of this evaluation, one value
-// read by every thread, so the whole grid builds or none of it does; clear
-// (null: none) is the other evaluation's flag, zeroed here.
-__global__ void __launch_bounds__(256) k_bonds(const double* __restrict__ pos, int64_t N, double Lx, double Ly,
-                                               double Lz, double iLx, double iLy, double iLz,
-                                               const int* __restrict__ nbr, const int* __restrict__ n_nb, double rb2,
-                                               int max_b, int* __restrict__ bnbr, int* __restrict__ bcount,
-                                               unsigned long long* __restrict__ mask, double* __restrict__ ref,
-                                               int* __restrict__ flags, const int* __restrict__ need,
-                                               int* __restrict__ clear) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (clear && i == 0) *clear = 0;
-  if (need && *need == 0) return;
-  const bool act = i < N;
-  const int n = act ? n_nb[i] : 0;
-  const double xi = act ? pos[3 * i] : 0.0, yi = act ? pos[3 * i + 1] : 0.0, zi = act ? pos[3 * i + 2] : 0.0;
-  int c = 0, found = 0;
-  unsigned long long m = 0;
-  // 16 list slots at a time, every load issued before the first distance
-  // (slots past the list read atom i itself and are masked out)
-  constexpr int U = 16;
-  for (int s0 = 0; s0 < n; s0 += U) {
-    int jj[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) jj[u] = s0 + u < n ? nbr[(int64_t)(s0 + u) * N + i] : (int)i;
-    double px[U], py[U], pz[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      px[u] = pos[3 * (int64_t)jj[u]];
-      py[u] = pos[3 * (int64_t)jj[u] + 1];
-      pz[u] = pos[3 * (int64_t)jj[u] + 2];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const double x = min_image(px[u] - xi, Lx, iLx);
-      const double y = min_image(py[u] - yi, Ly, iLy);
-      const double z = min_image(pz[u] - zi, Lz, iLz);
-      if (s0 + u < n && x * x + y * y + z * z < rb2) {
-        ++found;
-        m |= 1ull << (s0 + u);
-        if (c < max_b) bnbr[(int64_t)(c++) * N + i] = jj[u];
-      }
-    }
-  }
-  if (act) {
-    bcount[i] = c;
-    mask[i] = m;
-    ref[3 * i] = xi;
-    ref[3 * i + 1] = yi;
-    ref[3 * i + 2] = zi;
-  }
-  wave_atomic_max(&flags[0], found);
-  if (found > max_b) flags[1] = 1;
-}
-
 // --------------------------------------------------------------- potential
 __device__ __forceinline__ void cutoff_fn(const TersoffParams& p, double r, double* fc, double* dfc) {
   if (r < p.R - p.D) {
@@ -495,6 +424,12 @@ __device__ __forceinline__ void exp_fn(const TersoffParams& p, double x, double*
   *de = *e * p.m * p.l3m * xm1;
 }
 
+// List slot of the s-th kept pair of a bond mask (bit f: list slot f is kept).
+__device__ __forceinline__ int kept_slot(unsigned long long m, int s) {
+  for (int c = 0; c < s; ++c) m &= m - 1;
+  return __builtin_ctzll(m);
+}
+
 // LPA lanes per atom, SPL list slots per lane: lane s0 of the group handles
 // the pairs (i, j = nbr[s][i]) of the slots s = s0 + k LPA, k < SPL.  Each
 // pair's values go to LDS (field-major, sh[field][atom base + slot]) and
@@ -513,29 +448,48 @@ __global__ void __launch_bounds__(SITE_WG) k_tersoff_site(TersoffArgs a, Tersoff
   const int gb = (tid - s0) * SPL;   // this atom's slot 0 in LDS
   const int64_t N = a.N;
   const int64_t i = ((int64_t)blockIdx.x * SITE_WG + tid) / LPA;
-  const int n = i < N ? a.n_nb[i] : 0;
-  if (a.bond_need && *a.bond_need && n > 0) {
-    // reverse slots of freshly built bond lists: bond s of i sits at the
-    // s-th kept slot f of i's skin list, which is slot t = full_rev[f][i] in
-    // the list of j; its bond slot in j's list is the number of j's kept
-    // slots below t
-    const unsigned long long mi = a.bond_mask[i];
+  int n = 0;
+  if (a.bond_clear && blockIdx.x == 0 && tid == 0) *a.bond_clear = 0;
+  const bool build = a.bond_need && *a.bond_need;   // one value for the whole grid
+  if (!build) {
+    n = i < N ? a.n_nb[i] : 0;
+  } else {
+    // bond lists out of the skin lists (BondBufs): the listed pairs closer
+    // than rb in list order, LPA list slots at a time; their reverse slots
+    // need every atom's mask and come from the gather kernel
+    const int full = i < N ? a.full_n[i] : 0;
+    const int64_t ic = i < N ? i : 0;
+    const double xi = a.pos[3 * ic], yi = a.pos[3 * ic + 1], zi = a.pos[3 * ic + 2];
+    unsigned long long m = 0;
+    for (int f0 = 0; __ballot(f0 < full) != 0; f0 += LPA) {
+      bool keep = false;
+      if (f0 + s0 < full) {
+        const int64_t j = a.full_nbr[(int64_t)(f0 + s0) * N + i];
+        const double dx = min_image(a.pos[3 * j] - xi, a.box[0], a.ibox[0]);
+        const double dy = min_image(a.pos[3 * j + 1] - yi, a.box[1], a.ibox[1]);
+        const double dz = min_image(a.pos[3 * j + 2] - zi, a.box[2], a.ibox[2]);
+        keep = dx * dx + dy * dy + dz * dz < a.bond_rb2;
+      }
+      const unsigned long long hits = __ballot(keep) >> (tid - s0);
+      m |= (LPA == 64 ? hits : hits & ((1ull << (LPA & 63)) - 1ull)) << f0;
+    }
+    const int found = __builtin_popcountll(m);
+    n = found < a.max_nb ? found : a.max_nb;
+    if (i < N && s0 == 0) {
+      a.bond_n[i] = n;
+      a.bond_mask[i] = m;
+      a.bond_ref[3 * i] = xi;
+      a.bond_ref[3 * i + 1] = yi;
+      a.bond_ref[3 * i + 2] = zi;
+      if (found > a.max_nb) {
+        atomicMax(&a.bond_flags[0], found);
+        a.bond_flags[1] = 1;
+      }
+    }
 #pragma unroll
     for (int k = 0; k < SPL; ++k) {
       const int s = s0 + k * LPA;
-      if (s >= n) continue;
-      unsigned long long m = mi;
-      for (int c = 0; c < s; ++c) m &= m - 1;
-      const int f = __builtin_ctzll(m);
-      const int j = a.full_nbr[(int64_t)f * N + i];
-      const int t = a.full_rev[(int64_t)f * N + i];
-      int rr = -1;
-      if (t >= 0) {
-        const unsigned long long mj = a.bond_mask[j];
-        if ((mj >> t) & 1ull) rr = __builtin_popcountll(mj & ((1ull << t) - 1ull));
-      }
-      a.bond_rev[(int64_t)s * N + i] = rr;
-      if (rr < 0) a.bond_flags[2] = 1;
+      if (s < n) a.bond_nbr[(int64_t)s * N + i] = a.full_nbr[(int64_t)kept_slot(m, s) * N + i];
     }
   }
   double x[SPL], y[SPL], z[SPL], r[SPL], ir[SPL], fc[SPL], dfc[SPL], er[SPL], ea[SPL];
@@ -675,6 +629,10 @@ __device__ __forceinline__ void wave_lds_fence() {
 // of the partners' partials (24 contiguous bytes each).  Measured against one
 // lane summing and storing for its atom, partials in three planes, 8 lanes
 // for 4 bonds: 216000 Si atoms in MD 24.2 -> 16.0 us, 8000 atoms 6.2 -> 4.9 us.
+// The rest of an NVE step (half kicks, drift, displacement test) runs here
+// too, a component per lane: 216000 atoms 22 us instead of 16 + 7.3 us in a
+// kernel of its own, and one launch fewer (a step of 8000 atoms 20.4 -> 15.3 us
+// with the bond build in the site kernel instead of one that mostly exits).
 constexpr int GATHER_WG = 256;
 template <int LPA, int SPL>
 __global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, GatherArgs o) {
@@ -689,11 +647,24 @@ __global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, Gat
   double* tt = tot[wave];
   const int64_t N = a.N;
   const int64_t i0 = (int64_t)blockIdx.x * APB + (int64_t)wave * APW, i = i0 + g;
+  const bool built = a.bond_need && *a.bond_need;   // bond lists just built by the site kernel
   const int n = i < N ? a.n_nb[i] : 0;
   // the first round's list entry and reverse slot are loaded with the count,
   // not after it (the rows below max_nb exist; entries at or past n are not used)
   const bool row = i < N && s0 < a.max_nb;
   int jl = row ? a.nbr[(int64_t)s0 * N + i] : 0, rl = row ? a.rev[(int64_t)s0 * N + i] : 0;
+  // the reverse slots of new bond lists: bond s of i sits at the s-th kept
+  // slot f of i's skin list, which is slot t = full_rev[f][i] in the list of
+  // j; its bond slot in j's list is the number of j's kept slots below t
+  const unsigned long long mi = built && i < N ? a.bond_mask[i] : 0ull;
+  auto reverse_slot = [&](int s, int64_t j) -> int {
+    const int t = a.full_rev[(int64_t)kept_slot(mi, s) * N + i];
+    const unsigned long long mj = t >= 0 ? a.bond_mask[j] : 0ull;
+    const int r = t >= 0 && ((mj >> t) & 1ull) ? __builtin_popcountll(mj & ((1ull << t) - 1ull)) : -1;
+    a.bond_rev[(int64_t)s * N + i] = r;
+    if (r < 0) a.bond_flags[2] = 1;
+    return r < 0 ? 0 : r;   // the call fails at its end; no read out of range until then
+  };
   double sum[QL];
 #pragma unroll
   for (int q = 0; q < QL; ++q) sum[q] = 0.0;
@@ -708,6 +679,7 @@ __global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, Gat
       const int64_t es = (int64_t)s * N + i;
       if (k > 0) jl = a.nbr[es], rl = a.rev[es];
       const int64_t j = jl;
+      if (__builtin_expect(built, 0)) rl = reverse_slot(s, j);
       const double r[3] = {min_image(a.pos[3 * j] - a.pos[3 * i], a.box[0], a.ibox[0]),
                            min_image(a.pos[3 * j + 1] - a.pos[3 * i + 1], a.box[1], a.ibox[1]),
                            min_image(a.pos[3 * j + 2] - a.pos[3 * i + 2], a.box[2], a.ibox[2])};
@@ -740,7 +712,7 @@ __global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, Gat
     for (int q = 0; q < QL; ++q) tt[g * 12 + s0 * QL + q] = sum[q];
   }
   wave_lds_fence();
-  double mv2 = 0.0;
+  double mv2 = 0.0, d2 = 0.0;
   if (i < N && s0 < 3) {   // component s0 of atom i
     const double* t = tt + g * 12;
     double f = t[s0];
@@ -756,17 +728,36 @@ __global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, Gat
     }
     if (o.F) o.F[3 * i + s0] = f;
     if (o.kick_vel) {
-      // end of an NVT step: v += c F / m, then v *= exp(-xi dt / 2).  E_i's
-      // loads of v (the wave's own atoms) are back before any f is known, so
-      // before any component is written
+      // The rest of the step.  E_i's loads of v (the wave's own atoms) are back
+      // before any f is known, so before any component is written.
       const double m = o.mass[i];
       double v = o.kick_vel[3 * i + s0];
-      v = v + o.kick_c * f / m;
-      v = v * o.kick_scale[2];
+      if (o.kick2) {   // end of a step: v += c F / m, under a thermostat v *= exp(-xi dt / 2)
+        v = v + o.kick_c * f / m;
+        if (o.kick_scale) v = v * o.kick_scale[2];
+        if (o.kick_v32) o.kick_v32[3 * i + s0] = (float)v;
+        mv2 = m * v * v;
+      }
+      if (o.drift_pos) {   // start of the next: as k_md_step, into the other positions
+        v = v + o.kick_c * f / m;
+        const double L = a.box[s0];
+        double x = a.pos[3 * i + s0] + o.drift_dt * v;
+        x -= floor(x / L) * L;
+        if (x >= L) x -= L;
+        if (x < 0.0) x += L;
+        o.drift_pos[3 * i + s0] = x;
+        if (o.drift_ref) {
+          double d = x - o.drift_ref[3 * i + s0];
+          d -= L * rint(d / L);
+          d2 = d * d;
+        }
+      }
       o.kick_vel[3 * i + s0] = v;
-      if (o.kick_v32) o.kick_v32[3 * i + s0] = (float)v;
-      mv2 = m * v * v;
     }
+  }
+  if (o.drift_ref) {   // the bond lists' displacement test
+    const double y = __shfl(d2, lane + 1), z = __shfl(d2, lane + 2);
+    if (s0 == 0 && d2 + y + z > o.drift_thr2) *o.drift_need = 1;
   }
   // W of the wave's atoms, consecutive values by consecutive lanes
   const int64_t left = N - i0 < APW ? N - i0 : APW;
@@ -776,15 +767,19 @@ __global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, Gat
   if (o.W32)
     for (int e = lane; e < nw; e += 64) o.W32[9 * i0 + e] = (float)tt[e / 9 * 12 + 3 + e % 9];
   if (o.ke_part) {   // the work-group's partial sum of m v^2 after the kick (uniform over the launch)
+    // (with two slots per lane a work-group's atoms make two sums: the order
+    // of the total does not depend on the lanes per atom a list asks for)
+    constexpr int H = APB / SPL;
     __shared__ double kp[APB];
     const double y = __shfl(mv2, lane + 1), z = __shfl(mv2, lane + 2);
     if (s0 == 0) kp[tid / LPA] = (mv2 + y) + z;
     __syncthreads();
-    for (int w = APB / 2; w > 0; w >>= 1) {
-      if (tid < w) kp[tid] += kp[tid + w];
+#pragma unroll
+    for (int w = H / 2; w > 0; w >>= 1) {
+      if (tid < SPL * w) kp[tid / w * H + tid % w] += kp[tid / w * H + tid % w + w];
       __syncthreads();
     }
-    if (tid == 0) o.ke_part[blockIdx.x] = kp[0];
+    if (tid < SPL && (int64_t)blockIdx.x * APB + tid * H < N) o.ke_part[(int64_t)blockIdx.x * SPL + tid] = kp[tid * H];
   }
 }
 
@@ -793,17 +788,6 @@ static inline unsigned blocks_of(int64_t n, int t) { return (unsigned)((n + t - 
 
 hipError_t launch_zero_i32(hipStream_t s, int* p, int n) {
   hipLaunchKernelGGL(k_fill_zero_i32, dim3(blocks_of(n, 256)), dim3(256), 0, s, p, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_bonds(hipStream_t s, const double* pos, int64_t N, const double box[3], const int* nbr,
-                        const int* n_nb, double rb, int max_b, BondBufs b, bool reset_flags, const int* need,
-                        int* clear) {
-  if (reset_flags) hipLaunchKernelGGL(k_fill_zero_i32, dim3(1), dim3(256), 0, s, b.flags, 3);
-  const double rb2 = rb * rb * (1.0 + 1e-12);
-  hipLaunchKernelGGL(k_bonds, dim3(blocks_of(N, 256)), dim3(256), 0, s, pos, N, box[0], box[1], box[2], 1.0 / box[0],
-                     1.0 / box[1], 1.0 / box[2], nbr, n_nb, rb2, max_b, b.nbr, b.n_nb, b.mask, b.ref, b.flags, need,
-                     clear);
   return hipGetLastError();
 }
 
@@ -851,17 +835,12 @@ static hipError_t launch_pair_kernels(hipStream_t s, const TersoffArgs& a, const
 }
 
 // ------------------------------------------------ velocity Verlet (NVE)
-// The work between two force evaluations.  With MD_KICK2: the second half kick of step s, v += c F / m with c = dt / (2 KE)
-// (a = F / (m KE) in A/fs^2), and, with v32, that velocity in float32 (the
-// push's velocity input of step s).  With MD_KICK1_DRIFT: the first half
-// kick of step s + 1 with the same forces, then the drift x += dt v, wrapped
-// into [0, L) per axis (x - floor(x / L) L, then one correction step against
-// rounding at the edges), and, with ref, the bond lists' displacement test:
-// *need = 1 if the atom is farther than sqrt(thr2) from ref (its position at
-// the last bond build).  Each operation is the one the separate kick and
-// drift would make, in the same order.
-enum { MD_KICK2 = 1, MD_KICK1_DRIFT = 2 };
-
+// First half kick of a step and its drift in place, where they do not run in
+// the gather kernel (GatherArgs): v += c F / m with c = dt / (2 KE) (a = F /
+// (m KE) in A/fs^2), x += dt v wrapped into [0, L) per axis (x - floor(x / L) L,
+// then one correction step against rounding at the edges), and, with ref, the
+// bond lists' displacement test: *need = 1 if the atom is farther than
+// sqrt(thr2) from ref (its position at the last bond build).
 // One thread per atom component, 64 atoms (192 components, contiguous in
 // memory) per work-group; the displacement test sums each atom's three
 // squared components in LDS.
@@ -870,50 +849,40 @@ constexpr int MD_ATOMS = 64;
 __global__ void __launch_bounds__(3 * MD_ATOMS) k_md_step(double* __restrict__ pos, double* __restrict__ vel,
                                                           const double* __restrict__ F,
                                                           const double* __restrict__ mass, double c, double dt,
-                                                          double Lx, double Ly, double Lz, int64_t N, int parts,
-                                                          float* __restrict__ v32, const double* __restrict__ ref,
-                                                          double thr2, int* __restrict__ need) {
+                                                          double Lx, double Ly, double Lz, int64_t N,
+                                                          const double* __restrict__ ref, double thr2,
+                                                          int* __restrict__ need) {
   __shared__ double sh[3 * MD_ATOMS];
   const int t = threadIdx.x;
   const int64_t q = (int64_t)blockIdx.x * (3 * MD_ATOMS) + t;
   double d2 = 0.0;
   if (q < 3 * N) {
     const int a = (int)(q % 3);
-    const double m = mass[q / 3];
-    const double f = F[q];
     double v = vel[q];
-    if (parts & MD_KICK2) {
-      v = v + c * f / m;
-      if (v32) v32[q] = (float)v;
-    }
-    if (parts & MD_KICK1_DRIFT) {
-      v = v + c * f / m;
-      const double L = a == 0 ? Lx : (a == 1 ? Ly : Lz);
-      double x = pos[q] + dt * v;
-      x -= floor(x / L) * L;
-      if (x >= L) x -= L;
-      if (x < 0.0) x += L;
-      pos[q] = x;
-      if (ref) {
-        double d = x - ref[q];
-        d -= L * rint(d / L);
-        d2 = d * d;
-      }
-    }
+    v = v + c * F[q] / mass[q / 3];
+    const double L = a == 0 ? Lx : (a == 1 ? Ly : Lz);
+    double x = pos[q] + dt * v;
+    x -= floor(x / L) * L;
+    if (x >= L) x -= L;
+    if (x < 0.0) x += L;
+    pos[q] = x;
     vel[q] = v;
+    if (ref) {
+      double d = x - ref[q];
+      d -= L * rint(d / L);
+      d2 = d * d;
+    }
   }
-  if (!ref || !(parts & MD_KICK1_DRIFT)) return;   // uniform over the launch
+  if (!ref) return;   // uniform over the launch
   sh[t] = d2;
   __syncthreads();
   if (t < MD_ATOMS && sh[3 * t] + sh[3 * t + 1] + sh[3 * t + 2] > thr2) *need = 1;
 }
 
 hipError_t launch_md_step(hipStream_t s, double* pos, double* vel, const double* F, const double* mass, double c,
-                          double dt, const double box[3], int64_t N, bool kick2, bool kick1_drift, float* v32,
-                          const double* ref, double thr2, int* need) {
-  const int parts = (kick2 ? MD_KICK2 : 0) | (kick1_drift ? MD_KICK1_DRIFT : 0);
+                          double dt, const double box[3], int64_t N, const double* ref, double thr2, int* need) {
   hipLaunchKernelGGL(k_md_step, dim3(blocks_of(N, MD_ATOMS)), dim3(3 * MD_ATOMS), 0, s, pos, vel, F, mass, c, dt,
-                     box[0], box[1], box[2], N, parts, v32, ref, thr2, need);
+                     box[0], box[1], box[2], N, ref, thr2, need);
   return hipGetLastError();
 }
 
@@ -953,17 +922,42 @@ __global__ void __launch_bounds__(3 * MD_ATOMS) k_md_ke_partial(const double* __
   if (t == 0) part[blockIdx.x] = s;
 }
 
-// Thermostat update from the kinetic energy K = ke_unit / 2 sum of the
-// partials: mode & 1 (end of a step): eta += dt/2 xi, xi += dt/2 G; mode & 2
+// Thermostat update of the state from the kinetic energy K = ke_unit / 2 sum
+// of m v^2: mode & 1 (end of a step): eta += dt/2 xi, xi += dt/2 G; mode & 2
 // (start of a step): xi += dt/2 G, scale = exp(-xi dt / 2), eta += dt/2 xi;
-// G = (2K - gkt) / Q.  One work-group of 256 threads.
+// G = (2K - gkt) / Q.
+__device__ __forceinline__ void thermostat_update(double sum, double st[4], const ThermostatArgs& th, int mode) {
+  const double K = 0.5 * sum * th.ke_unit;
+  const double G = (2.0 * K - th.gkt) / th.Q;
+  double xi = st[0], eta = st[1];
+  if (mode & 1) {
+    eta += 0.5 * th.dt * xi;
+    xi += 0.5 * th.dt * G;
+  }
+  if (mode & 2) {
+    xi += 0.5 * th.dt * G;
+    st[2] = exp(-0.5 * th.dt * xi);
+    eta += 0.5 * th.dt * xi;
+  }
+  st[0] = xi;
+  st[1] = eta;
+  st[3] = K;
+}
+
+// The update by one work-group of 256 threads, from state `from` into `to`.
 __global__ void __launch_bounds__(256) k_thermostat(const double* __restrict__ part, int64_t n_part,
-                                                    double* __restrict__ st, double dt, double Q, double gkt,
-                                                    double ke_unit, int mode) {
+                                                    const double* from, double* to, ThermostatArgs th, int mode) {
   __shared__ double sh[256];
   const int t = threadIdx.x;
   double acc = 0.0;
-  for (int64_t k = t; k < n_part; k += 256) acc += part[k];
+  for (int64_t k0 = t; k0 < n_part; k0 += 8 * 256) {   // eight loads at a time, added in order
+    double x[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = part[k0 + 256 * q < n_part ? k0 + 256 * q : n_part - 1];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (k0 + 256 * q < n_part) acc += x[q];
+  }
   sh[t] = acc;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
@@ -971,43 +965,67 @@ __global__ void __launch_bounds__(256) k_thermostat(const double* __restrict__ p
     __syncthreads();
   }
   if (t != 0) return;
-  const double K = 0.5 * sh[0] * ke_unit;
-  const double G = (2.0 * K - gkt) / Q;
-  double xi = st[0], eta = st[1];
-  if (mode & 1) {
-    eta += 0.5 * dt * xi;
-    xi += 0.5 * dt * G;
-  }
-  if (mode & 2) {
-    xi += 0.5 * dt * G;
-    st[2] = exp(-0.5 * dt * xi);
-    eta += 0.5 * dt * xi;
-  }
-  st[0] = xi;
-  st[1] = eta;
-  st[3] = K;
+  double st[4] = {from[0], from[1], from[2], from[3]};
+  thermostat_update(sh[0], st, th, mode);
+  for (int q = 0; q < 4; ++q) to[q] = st[q];
 }
 
 // Start of a step under the thermostat: the scale st[2], the first half kick,
-// the drift and the bond lists' displacement test, as k_md_step.
+// the drift and the bond lists' displacement test, as k_md_step.  With n_part
+// > 0 every work-group first takes the thermostat update itself (the same sum
+// in the same order in each, work-group 0 writes the state to `to`), which
+// saves a launch of one work-group per step: an MD step of 8000 atoms is a
+// chain of short kernels.  n_part = 0: the update is already in `to`.
 __global__ void __launch_bounds__(3 * MD_ATOMS) k_md_nvt_start(double* __restrict__ pos, double* __restrict__ vel,
                                                                const double* __restrict__ F,
                                                                const double* __restrict__ mass, double c, double dt,
                                                                double Lx, double Ly, double Lz, int64_t N,
-                                                               const double* __restrict__ st,
+                                                               const double* __restrict__ part, int n_part,
+                                                               const double* __restrict__ from, double* to,
+                                                               ThermostatArgs th, int mode,
                                                                const double* __restrict__ ref, double thr2,
                                                                int* __restrict__ need) {
   __shared__ double sh[3 * MD_ATOMS];
+  __shared__ double new_scale;
   const int t = threadIdx.x;
   const int64_t q = (int64_t)blockIdx.x * (3 * MD_ATOMS) + t;
+  const bool act = q < 3 * N;
+  double v = act ? vel[q] : 0.0, x = act ? pos[q] : 0.0;
+  const double f = act ? F[q] : 0.0, m = act ? mass[q / 3] : 1.0;
+  double scale;
+  if (n_part > 0) {
+    if (t < 64) {   // one wave; k_thermostat's sum: its threads' values, then its tree
+      double p[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int k0 = 0; k0 < n_part; k0 += 256)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int k = k0 + 64 * q + t;
+          p[q] += k < n_part ? part[k] : 0.0;
+        }
+      double sum = (p[0] + p[2]) + (p[1] + p[3]);
+#pragma unroll
+      for (int w = 32; w > 0; w >>= 1) sum += __shfl_down(sum, w);
+      if (t == 0) sh[0] = sum;
+    }
+    if (t == 0) {
+      double st[4] = {from[0], from[1], from[2], from[3]};
+      thermostat_update(sh[0], st, th, mode);
+      new_scale = st[2];
+      if (blockIdx.x == 0)
+        for (int k = 0; k < 4; ++k) to[k] = st[k];
+    }
+    __syncthreads();
+    scale = new_scale;
+  } else {
+    scale = to[2];
+  }
   double d2 = 0.0;
-  if (q < 3 * N) {
+  if (act) {
     const int a = (int)(q % 3);
-    const double m = mass[q / 3];
-    double v = vel[q] * st[2];
-    v = v + c * F[q] / m;
+    v = v * scale;
+    v = v + c * f / m;
     const double L = a == 0 ? Lx : (a == 1 ? Ly : Lz);
-    double x = pos[q] + dt * v;
+    x = x + dt * v;
     x -= floor(x / L) * L;
     if (x >= L) x -= L;
     if (x < 0.0) x += L;
@@ -1020,6 +1038,7 @@ __global__ void __launch_bounds__(3 * MD_ATOMS) k_md_nvt_start(double* __restric
     }
   }
   if (!ref) return;   // uniform over the launch
+  __syncthreads();
   sh[t] = d2;
   __syncthreads();
   if (t < MD_ATOMS && sh[3 * t] + sh[3 * t + 1] + sh[3 * t + 2] > thr2) *need = 1;
@@ -1041,19 +1060,29 @@ hipError_t launch_md_ke_partial(hipStream_t s, const double* vel, const double* 
   return hipGetLastError();
 }
 
-hipError_t launch_thermostat(hipStream_t s, const double* part, int64_t n_part, double* st, double dt, double Q,
-                             double gkt, double ke_unit, int mode) {
-  hipLaunchKernelGGL(k_thermostat, dim3(1), dim3(256), 0, s, part, n_part, st, dt, Q, gkt, ke_unit, mode);
+hipError_t launch_thermostat(hipStream_t s, const double* part, int64_t n_part, const double* from, double* to,
+                             const ThermostatArgs& th, int mode) {
+  hipLaunchKernelGGL(k_thermostat, dim3(1), dim3(256), 0, s, part, n_part, from, to, th, mode);
   return hipGetLastError();
 }
 
-int64_t gather_blocks(int64_t N, int lpa) { return (int64_t)blocks_of(N * (lpa == 8 ? 4 : lpa), GATHER_WG); }
+int64_t gather_parts(int64_t N, int lpa) { return (int64_t)blocks_of(N * lpa, GATHER_WG); }
 
 hipError_t launch_md_nvt_start(hipStream_t s, double* pos, double* vel, const double* F, const double* mass, double c,
-                               double dt, const double box[3], int64_t N, const double* st, const double* ref,
+                               double dt, const double box[3], int64_t N, const double* part, int64_t n_part,
+                               const double* from, double* to, const ThermostatArgs& th, int mode, const double* ref,
                                double thr2, int* need) {
+  // Summing the partials in every work-group is cheaper than a launch while
+  // there are few of them (512: 16384 atoms, 256 work-groups); the reads grow
+  // with the square of the size.
+  constexpr int64_t INLINE_PARTS = 512;
+  if (n_part > INLINE_PARTS) {
+    const hipError_t e = launch_thermostat(s, part, n_part, from, to, th, mode);
+    if (e != hipSuccess) return e;
+    n_part = 0;
+  }
   hipLaunchKernelGGL(k_md_nvt_start, dim3((unsigned)md_nvt_parts(N)), dim3(3 * MD_ATOMS), 0, s, pos, vel, F, mass, c,
-                     dt, box[0], box[1], box[2], N, st, ref, thr2, need);
+                     dt, box[0], box[1], box[2], N, part, (int)n_part, from, to, th, mode, ref, thr2, need);
   return hipGetLastError();
 }
 

@@ -74,16 +74,25 @@ struct TersoffArgs {
   int max_nb;
   double* dd;
   double* U;
-  // Bond lists (nbr, n_nb above) just rebuilt from the skin lists: when
-  // bond_need is not null and *bond_need != 0 the site kernel also writes
-  // their reverse slots to bond_rev (which rev must then point to) from the
-  // skin lists' full_nbr / full_rev and the kept-slot masks; bond_flags[2] = 1
-  // if one is missing.
+  // Bond lists (nbr, n_nb, rev above): when bond_need is not null and
+  // *bond_need != 0 the site kernel first builds them out of the skin lists
+  // (full_n, full_nbr, full_rev: the pairs closer than sqrt(bond_rb2), at most
+  // max_nb per atom, and the positions at the build) and the gather kernel
+  // their reverse slots, through the views below (which nbr, n_nb and rev then
+  // point to).  bond_flags[0] = largest count and [1] = 1 if an atom had more
+  // than max_nb, [2] = 1 if a reverse slot is missing.  bond_clear (may be
+  // null): the other evaluation's rebuild flag, zeroed by the site kernel.
   const int* bond_need;
-  const unsigned long long* bond_mask;
+  int* bond_clear;
+  double bond_rb2;
+  const int* full_n;
   const int* full_nbr;
   const int* full_rev;
+  int* bond_nbr;
+  int* bond_n;
   int* bond_rev;
+  unsigned long long* bond_mask;
+  double* bond_ref;
   int* bond_flags;
 };
 
@@ -101,14 +110,25 @@ struct GatherArgs {
   float* W32;
   double* Fext;
   bool add_ext;               // F = interatomic force + F_ext (needs fe; vel for E_i)
-  // The end of an NVT step on the fly (kick_vel null: none): v += kick_c F / m,
-  // v *= kick_scale[2] on kick_vel (after E_i has read vel), its float32 copy to
-  // kick_v32 (may be null), and per work-group the sum of m v^2 to ke_part.
+  // The steps between two evaluations on the fly (kick_vel null: none), on
+  // kick_vel after E_i has read vel.  kick2: the end of a step, v += kick_c
+  // F / m, with kick_scale v *= kick_scale[2], the float32 copy to kick_v32
+  // (may be null) and per work-group the sum of m v^2 to ke_part (may be null).
+  // drift_pos (null: none): the start of the next step, v += kick_c F / m and
+  // drift_pos = the evaluation's positions + drift_dt v, wrapped into the box
+  // (another array: the launch still reads the positions), and with drift_ref
+  // *drift_need = 1 if the atom is farther than sqrt(drift_thr2) from it.
   double* kick_vel;
   double kick_c;
+  bool kick2;
   const double* kick_scale;
   float* kick_v32;
   double* ke_part;
+  double* drift_pos;
+  double drift_dt;
+  const double* drift_ref;
+  double drift_thr2;
+  int* drift_need;
 };
 
 // Lists of the pairs closer than rc; also counts, per atom, those closer
@@ -117,15 +137,6 @@ hipError_t launch_neighbors(hipStream_t s, const double* pos, int64_t N, const C
                             int max_nb, NeighborBufs b);
 // Zero n ints (n > 0).
 hipError_t launch_zero_i32(hipStream_t s, int* p, int n);
-// Bond lists out of the lists (nbr, n_nb): every pair closer than rb, at
-// most max_b per atom (max_nb <= 64), and their kept-slot masks (their
-// reverse slots come from the next site kernel: TersoffArgs.bond_need).  The
-// flags accumulate over launches unless reset_flags clears them first.  need
-// (null: always) makes the build conditional on *need != 0, decided on the
-// device; clear (null: none) is zeroed.
-hipError_t launch_bonds(hipStream_t s, const double* pos, int64_t N, const double box[3], const int* nbr,
-                        const int* n_nb, double rb, int max_b, BondBufs b, bool reset_flags, const int* need,
-                        int* clear);
 hipError_t launch_set_i32(hipStream_t s, int* p, int value);
 // Lanes per atom of the evaluation kernels for a largest neighbour count:
 // the next power of two, at least 4 (64 at most: max_nb <= 64).
@@ -136,31 +147,32 @@ int tersoff_lanes(int max_count);
 hipError_t launch_tersoff(hipStream_t s, const TersoffArgs& a, const TersoffParams& p, const GatherArgs& o, int lpa,
                           hipEvent_t e0, hipEvent_t e1, hipEvent_t e2);
 
-// Velocity Verlet between two force evaluations on [N][3] float64 arrays:
-// kick2 = the second half kick of a step, vel += c F / mass (v32: the result
-// also in float32, NULL to skip); kick1_drift = the first half kick of the
-// next step with the same F, then the drift pos += dt vel wrapped into the
-// box, and with ref (NULL: none) *need = 1 if an atom is farther than
-// sqrt(thr2) from its position in ref.
+// First half kick of a velocity-Verlet step and its drift, in place on [N][3]
+// float64 arrays: vel += c F / mass, pos += dt vel wrapped into the box, and
+// with ref (NULL: none) *need = 1 if an atom is farther than sqrt(thr2) from
+// its position in ref.  (Elsewhere they run in the gather kernel.)
 hipError_t launch_md_step(hipStream_t s, double* pos, double* vel, const double* F, const double* mass, double c,
-                          double dt, const double box[3], int64_t N, bool kick2, bool kick1_drift, float* v32,
-                          const double* ref, double thr2, int* need);
+                          double dt, const double box[3], int64_t N, const double* ref, double thr2, int* need);
 
-// Nose-Hoover thermostat steps (state st [4] on the device: xi, eta, the
-// velocity scale exp(-xi dt/2), the last kinetic energy).  ke_partial: sums
-// of m v^2, one per 64 atoms (md_nvt_parts of them); thermostat: mode 1
-// end-of-step, 2 start-of-step, 3 both, from n_part partials; start: the
-// scale, the first half kick and the drift (ref, thr2, need as for
-// launch_md_step).  The end of a step runs in the gather kernel
-// (GatherArgs.kick_vel).
+// Nose-Hoover thermostat steps (states of 4 doubles on the device: xi, eta,
+// the velocity scale exp(-xi dt/2), the last kinetic energy; an update reads
+// one and writes the other).  ke_partial: sums of m v^2, one per 64 atoms
+// (md_nvt_parts of them); thermostat: mode 1 end-of-step, 2 start-of-step, 3
+// both, from n_part partials; start: the update (mode 2 or 3), then the scale,
+// the first half kick and the drift (ref, thr2, need as for launch_md_step).
+// The end of a step runs in the gather kernel (GatherArgs.kick_vel).
+struct ThermostatArgs {
+  double dt, Q, gkt, ke_unit;
+};
 int64_t md_nvt_parts(int64_t N);
 hipError_t launch_md_ke_partial(hipStream_t s, const double* vel, const double* mass, int64_t N, double* part);
-hipError_t launch_thermostat(hipStream_t s, const double* part, int64_t n_part, double* st, double dt, double Q,
-                             double gkt, double ke_unit, int mode);
-// Work-groups of the gather kernel for lpa lanes per atom (its ke_part count).
-int64_t gather_blocks(int64_t N, int lpa);
+hipError_t launch_thermostat(hipStream_t s, const double* part, int64_t n_part, const double* from, double* to,
+                             const ThermostatArgs& th, int mode);
+// m v^2 sums that the gather kernel writes to ke_part for lists of lpa lanes per atom.
+int64_t gather_parts(int64_t N, int lpa);
 hipError_t launch_md_nvt_start(hipStream_t s, double* pos, double* vel, const double* F, const double* mass, double c,
-                               double dt, const double box[3], int64_t N, const double* st, const double* ref,
+                               double dt, const double box[3], int64_t N, const double* part, int64_t n_part,
+                               const double* from, double* to, const ThermostatArgs& th, int mode, const double* ref,
                                double thr2, int* need);
 hipError_t launch_thermostat_set(hipStream_t s, double* st, double xi, double eta);
 

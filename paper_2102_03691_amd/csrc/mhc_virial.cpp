@@ -47,7 +47,8 @@ struct mhc_virial {
   NeighborBufs nb{};
   double *d_dd = nullptr, *d_U = nullptr;
   double* d_F = nullptr;  // forces of the molecular dynamics (mhc_virial_md)
-  double* d_thermo = nullptr;   // Nose-Hoover state [4] (mhc_virial_md_nvt)
+  double* d_pos2 = nullptr;     // second positions array of mhc_virial_md (drifts in the gather kernel)
+  double* d_thermo = nullptr;   // Nose-Hoover states [2][4] (mhc_virial_md_nvt)
   double* d_kepart = nullptr;   // kinetic-energy partials (per 64 atoms, or per gather work-group)
   // Bond lists of the molecular dynamics when the lists carry a skin: the
   // pairs inside R + D + delta (delta = bond_skin, the smaller of the skin and
@@ -250,8 +251,8 @@ mhc_status mhc_virial_create(int device, void* hip_stream, int64_t n_atoms, cons
             valloc(v, 3 * N, &b.cpos) && valloc(v, n_cells, &b.count) && valloc(v, n_cells + 1, &b.start) &&
             valloc(v, (n_cells + 1023) / 1024, &b.tile_sums) && valloc(v, (N + 15) / 16, &b.most) && valloc(v, 3, &b.flags) &&
             valloc(v, 3 * MN, &v->d_dd) && valloc(v, N, &v->d_U) && valloc(v, 3 * N, &v->d_F) &&
-            valloc(v, 4, &v->d_thermo) &&
-            valloc(v, std::max(md_nvt_parts(N), gather_blocks(N, 64)), &v->d_kepart) &&
+            valloc(v, 8, &v->d_thermo) && valloc(v, 3 * N, &v->d_pos2) &&
+            valloc(v, std::max(md_nvt_parts(N), gather_parts(N, 64)), &v->d_kepart) &&
             valloc(v, MN, &v->bb.nbr) && valloc(v, MN, &v->bb.rev) && valloc(v, N, &v->bb.n_nb) &&
             valloc(v, N, &v->bb.mask) && valloc(v, 3 * N, &v->bb.ref) && valloc(v, 12, &v->bb.flags);
   if (!ok) return cleanup(MHC_ERR_OOM, "device allocation failed");
@@ -396,6 +397,7 @@ mhc_status md_run(mhc_virial* v, double* pos, double* vel, double dt, int32_t n_
   VHIP_TRY(hipSetDevice(v->device), "hipSetDevice");
   const int64_t N = v->N;
   bool any_compact = false;
+  double *th_now = v->d_thermo, *th_next = v->d_thermo + 4;   // thermostat states
   // Evaluation e (0: the entry positions, s + 1: after step s) rebuilds the
   // bond lists if need[e & 1] != 0, which the drift before it sets when an
   // atom has moved more than half the bond lists' skin since their build.
@@ -403,12 +405,17 @@ mhc_status md_run(mhc_virial* v, double* pos, double* vel, double dt, int32_t n_
   const double thr2 = half * half * (1.0 - 1e-9);
   int64_t e_idx = 0;
   const double c = 0.5 * dt / KE_UNIT_EV;   // half kick: dv = dt/2 F / (m KE)
-  int64_t gather_parts = 0;   // work-groups of the last gather launch
-  // kick_v32: with nvt, the end of the step on the fly in the gather kernel
-  // (second half kick, thermostat scale, float32 velocities, m v^2 partials)
-  auto force = [&](float* w32, bool kick_end = false, float* kick_v32 = nullptr) -> mhc_status {
+  int64_t ke_parts = 0;   // m v^2 sums of the last gather launch
+  // the positions of the next evaluation: the caller's array, or v->d_pos2
+  // after an odd number of drifts in the gather kernel
+  double* cur = pos;
+  // What runs in the gather kernel after the forces: kick2 = the second half
+  // kick of the step (with nvt also the thermostat scale and the m v^2
+  // partials) and its float32 velocities; drift = the next step's first half
+  // kick and drift (NVE), into the other positions array.
+  auto force = [&](float* w32, bool kick2, float* kick_v32, bool drift) -> mhc_status {
     TersoffArgs a{};
-    a.pos = pos;
+    a.pos = cur;
     a.N = N;
     for (int q = 0; q < 3; ++q) a.box[q] = v->box[q], a.ibox[q] = 1.0 / v->box[q];
     a.nbr = v->nb.nbr;
@@ -416,21 +423,22 @@ mhc_status md_run(mhc_virial* v, double* pos, double* vel, double dt, int32_t n_
     a.rev = v->nb.rev;
     a.max_nb = v->max_nb;
     int lpa = v->lpa;
+    const int sl = (int)(e_idx & 1);
     if (v->compact) {   // bond lists out of the skin lists, rebuilt when the atoms have moved enough
       any_compact = true;
-      const int sl = (int)(e_idx & 1);
-      VHIP_TRY(launch_bonds(v->stream, pos, N, v->box, v->nb.nbr, v->nb.n_nb, v->tp.R + v->tp.D + v->bond_skin,
-                            v->max_b, v->bb, false, v->bb.need + sl, v->bb.need + (sl ^ 1)),
-               "bonds");
-      a.nbr = v->bb.nbr;
-      a.n_nb = v->bb.n_nb;
-      a.rev = v->bb.rev;
+      const double rb = v->tp.R + v->tp.D + v->bond_skin;
+      a.nbr = a.bond_nbr = v->bb.nbr;
+      a.n_nb = a.bond_n = v->bb.n_nb;
+      a.rev = a.bond_rev = v->bb.rev;
       a.max_nb = v->max_b;
-      a.bond_need = v->bb.need + sl;   // the site kernel fills their reverse slots after a rebuild
-      a.bond_mask = v->bb.mask;
+      a.bond_need = v->bb.need + sl;
+      a.bond_clear = v->bb.need + (sl ^ 1);
+      a.bond_rb2 = rb * rb * (1.0 + 1e-12);
+      a.full_n = v->nb.n_nb;
       a.full_nbr = v->nb.nbr;
       a.full_rev = v->nb.rev;
-      a.bond_rev = v->bb.rev;
+      a.bond_mask = v->bb.mask;
+      a.bond_ref = v->bb.ref;
       a.bond_flags = v->bb.flags;
       lpa = v->lpa_b;
     }
@@ -440,79 +448,96 @@ mhc_status md_run(mhc_virial* v, double* pos, double* vel, double dt, int32_t n_
     o.mass = v->d_mass;
     o.ke_unit = KE_UNIT_EV;
     o.rcut2 = rcut2_of(v);
-    o.F = v->d_F;
+    o.F = drift ? nullptr : v->d_F;
     o.W32 = w32;
     if (nvt && nvt->drive) {   // F + F_ext (Eq. 12), E_i from the velocities now
       o.add_ext = true;
       o.vel = vel;
       for (int q = 0; q < 3; ++q) o.fe[q] = nvt->fe[q];
     }
-    if (kick_end) {
+    if (kick2 || drift) {
       o.kick_vel = vel;
       o.kick_c = c;
-      o.kick_scale = v->d_thermo;
+      o.kick2 = kick2;
       o.kick_v32 = kick_v32;
-      o.ke_part = v->d_kepart;
+      if (nvt) {
+        o.kick_scale = th_now;
+        o.ke_part = v->d_kepart;
+      }
     }
-    gather_parts = gather_blocks(N, lpa);
+    if (drift) {
+      o.drift_pos = cur == pos ? v->d_pos2 : pos;
+      o.drift_dt = dt;
+      if (v->compact) {
+        o.drift_ref = v->bb.ref;
+        o.drift_thr2 = thr2;
+        o.drift_need = v->bb.need + (sl ^ 1);
+      }
+    }
+    ke_parts = gather_parts(N, lpa);
     hipEvent_t e[3] = {nullptr, nullptr, nullptr};
     mhc_status s2 = timing_events(v, e);
     if (s2) return s2;
     VHIP_TRY(launch_tersoff(v->stream, a, v->tp, o, lpa, e[0], e[1], e[2]), "force kernels");
+    if (drift) cur = o.drift_pos;
     return MHC_OK;
   };
-  // overflow and reverse-slot flags of the bond passes accumulate over this call's steps
+  auto rebuild_lists = [&](int32_t s) -> mhc_status {   // before the force of step s
+    if (rebuild <= 0 || (s + 1) % rebuild != 0) return MHC_OK;
+    mhc_status s2 = mhc_virial_neighbors(v, cur, nullptr);
+    if (s2) {
+      // the caller's array receives the positions that were searched
+      if (cur != pos && s2 != MHC_ERR_HIP)
+        (void)hipMemcpyAsync(pos, cur, (size_t)N * 3 * 8, hipMemcpyDeviceToDevice, v->stream);
+      return s2;
+    }
+    // new lists (and possibly new bond slots): the bond lists follow them
+    VHIP_TRY(launch_set_i32(v->stream, v->bb.need + (e_idx & 1), 1), "bond rebuild flag");
+    return MHC_OK;
+  };
+  // overflow and reverse-slot flags of the bond builds accumulate over this call's steps
   VHIP_TRY(launch_zero_i32(v->stream, v->bb.flags, 3), "clear bond flags");
   VHIP_TRY(launch_set_i32(v->stream, v->bb.need, 1), "bond rebuild flag");   // the entry evaluation builds
-  if ((st = force(nullptr))) return st;     // forces at the entry positions
   if (nvt) {
-    // thermostat half steps around each velocity-Verlet step
-    VHIP_TRY(launch_thermostat_set(v->stream, v->d_thermo, nvt->state[0], nvt->state[1]), "thermostat state");
+    // thermostat half steps around each velocity-Verlet step; its state
+    // alternates between two slots
+    if ((st = force(nullptr, false, nullptr, false))) return st;   // forces at the entry positions
+    const ThermostatArgs th{dt, nvt->Q, nvt->gkt, KE_UNIT_EV};
+    VHIP_TRY(launch_thermostat_set(v->stream, th_now, nvt->state[0], nvt->state[1]), "thermostat state");
     VHIP_TRY(launch_md_ke_partial(v->stream, vel, v->d_mass, N, v->d_kepart), "kinetic energy");
-    VHIP_TRY(launch_thermostat(v->stream, v->d_kepart, md_nvt_parts(N), v->d_thermo, dt, nvt->Q, nvt->gkt,
-                               KE_UNIT_EV, 2),
-             "thermostat");
+    int64_t parts = md_nvt_parts(N);
     for (int32_t s = 0; s < n_steps; ++s) {
       e_idx = s + 1;
-      VHIP_TRY(launch_md_nvt_start(v->stream, pos, vel, v->d_F, v->d_mass, c, dt, v->box, N, v->d_thermo,
-                                   v->compact ? v->bb.ref : nullptr, thr2, v->bb.need + (e_idx & 1)),
+      VHIP_TRY(launch_md_nvt_start(v->stream, pos, vel, v->d_F, v->d_mass, c, dt, v->box, N, v->d_kepart, parts, th_now,
+                                   th_next, th, s > 0 ? 3 : 2, v->compact ? v->bb.ref : nullptr, thr2,
+                                   v->bb.need + (e_idx & 1)),
                "kick and drift");
-      if (rebuild > 0 && (s + 1) % rebuild == 0) {
-        if ((st = mhc_virial_neighbors(v, pos, nullptr))) return st;
-        VHIP_TRY(launch_set_i32(v->stream, v->bb.need + (e_idx & 1), 1), "bond rebuild flag");
-      }
+      std::swap(th_now, th_next);
+      if ((st = rebuild_lists(s))) return st;
       // the force, and the end of the step in the same gather kernel
-      if ((st = force(W32 ? W32 + (int64_t)s * N * 9 : nullptr, true, v32 ? v32 + (int64_t)s * N * 3 : nullptr)))
+      if ((st = force(W32 ? W32 + (int64_t)s * N * 9 : nullptr, true, v32 ? v32 + (int64_t)s * N * 3 : nullptr, false)))
         return st;
-      VHIP_TRY(launch_thermostat(v->stream, v->d_kepart, gather_parts, v->d_thermo, dt, nvt->Q, nvt->gkt,
-                                 KE_UNIT_EV, s + 1 < n_steps ? 3 : 1),
-               "thermostat");
+      parts = ke_parts;
     }
+    VHIP_TRY(launch_thermostat(v->stream, v->d_kepart, parts, th_now, th_next, th, 1), "thermostat");
+    std::swap(th_now, th_next);
   } else {
-    // kicks and drifts: before step s's force the first half kick and drift of
-    // step s (fused with the second half kick of step s - 1 from s = 1 on);
-    // after the last force its second half kick alone
-    auto kick_drift = [&](int32_t s) -> mhc_status {
-      e_idx = s + 1;   // the evaluation after this drift
-      const bool track = v->compact;
-      VHIP_TRY(launch_md_step(v->stream, pos, vel, v->d_F, v->d_mass, c, dt, v->box, N, s > 0, true,
-                              s > 0 && v32 ? v32 + (int64_t)(s - 1) * N * 3 : nullptr, track ? v->bb.ref : nullptr,
-                              thr2, v->bb.need + (e_idx & 1)),
+    // Evaluation s + 1 ends step s and, in the same gather kernel, starts step
+    // s + 1 into the other positions array.  With an odd number of steps the
+    // first drift runs in place, so that the last one lands in the caller's array.
+    const bool in_place = n_steps % 2 != 0;
+    if ((st = force(nullptr, false, nullptr, !in_place))) return st;   // forces at the entry positions
+    if (in_place)
+      VHIP_TRY(launch_md_step(v->stream, pos, vel, v->d_F, v->d_mass, c, dt, v->box, N,
+                              v->compact ? v->bb.ref : nullptr, thr2, v->bb.need + 1),
                "kick and drift");
-      return MHC_OK;
-    };
     for (int32_t s = 0; s < n_steps; ++s) {
-      if ((st = kick_drift(s))) return st;
-      if (rebuild > 0 && (s + 1) % rebuild == 0) {
-        if ((st = mhc_virial_neighbors(v, pos, nullptr))) return st;
-        // new lists (and possibly new bond slots): the bond lists follow them
-        VHIP_TRY(launch_set_i32(v->stream, v->bb.need + (e_idx & 1), 1), "bond rebuild flag");
-      }
-      if ((st = force(W32 ? W32 + (int64_t)s * N * 9 : nullptr))) return st;
+      e_idx = s + 1;
+      if ((st = rebuild_lists(s))) return st;
+      if ((st = force(W32 ? W32 + (int64_t)s * N * 9 : nullptr, true, v32 ? v32 + (int64_t)s * N * 3 : nullptr,
+                      s + 1 < n_steps)))
+        return st;
     }
-    VHIP_TRY(launch_md_step(v->stream, pos, vel, v->d_F, v->d_mass, c, dt, v->box, N, true, false,
-                            v32 ? v32 + (int64_t)(n_steps - 1) * N * 3 : nullptr, nullptr, 0.0, nullptr),
-             "half kick");
   }
   if (F) VHIP_TRY(hipMemcpyAsync(F, v->d_F, (size_t)N * 3 * 8, hipMemcpyDeviceToDevice, v->stream), "copy forces");
   if (any_compact) {
@@ -528,7 +553,7 @@ mhc_status md_run(mhc_virial* v, double* pos, double* vel, double dt, int32_t n_
   }
   if (nvt) {
     const double* th = static_cast<const double*>(v->h_read);
-    VHIP_TRY(hipMemcpyAsync(v->h_read, v->d_thermo, 4 * sizeof(double), hipMemcpyDeviceToHost, v->stream), "read thermostat");
+    VHIP_TRY(hipMemcpyAsync(v->h_read, th_now, 4 * sizeof(double), hipMemcpyDeviceToHost, v->stream), "read thermostat");
     VHIP_TRY(hipStreamSynchronize(v->stream), "md sync");
     nvt->state[0] = th[0];
     nvt->state[1] = th[1];
