@@ -426,45 +426,87 @@ hipError_t launch_corr(hipStream_t s, const double* X, int64_t ldx, int t_count,
 }
 
 // ----------------------------------------------------------------- read-out
+// Work-group = 64 series q = (r, nu) over all lags, 64 lags at a time: the sums
+// come in along the lags (contiguous), the running integral of a series is
+// taken by one thread in LDS, and both go out along the series (contiguous).
+// One thread per series read its sums L doubles apart from its neighbours':
+// 500 lags x 4509 series 171 us, now 60 us.
+constexpr int CF_T = 64;   // series and lags per tile
 __global__ void __launch_bounds__(256) k_corr_finish(const double* __restrict__ csum, const double* __restrict__ ccomp,
                                                      const double* __restrict__ psum, const double* __restrict__ pcomp,
-                                                     int64_t R3, int L, int64_t S, double dt,
-                                                     double* __restrict__ corr, double* __restrict__ integral) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // series (r, nu)
-  if (q >= R3 * 3) return;
-  double G = 0.0, prev = 0.0;
-  for (int tau = 0; tau < L; ++tau) {
-    const int64_t src = q * L + tau;               // sums are lag-contiguous
-    const int64_t o = (int64_t)tau * R3 * 3 + q;   // output [tau][r][nu]
+                                                     int64_t n_binned, int L, int64_t S, double dt,
+                                                     double* __restrict__ corr, double* __restrict__ integral,
+                                                     double* __restrict__ hcacf) {
+  __shared__ double cs[CF_T][CF_T + 1], gs[CF_T][CF_T + 1];   // [series][lag]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t n_q = n_binned + 9, q0 = (int64_t)blockIdx.x * CF_T;
+  double G = 0.0, prev = 0.0;                                 // of series q0 + lane (wave 0)
+  for (int t0 = 0; t0 < L; t0 += CF_T) {
+    const int tau = min(t0 + lane, L - 1);
     const int64_t cnt = S - tau;
-    double sum = csum[src] + ccomp[src];
-    if (psum) sum += psum[src] + pcomp[src];       // steps not yet in the running sums
-    const double c = (cnt > 0) ? sum / (double)cnt : 0.0;
-    corr[o] = c;
-    if (tau > 0) G += dt * 0.5 * (prev + c);
-    integral[o] = G;
-    prev = c;
+#pragma unroll 4
+    for (int k = wave; k < CF_T; k += 4) {
+      const int64_t src = min(q0 + k, n_q - 1) * L + tau;
+      double sum = csum[src] + ccomp[src];
+      if (psum) sum += psum[src] + pcomp[src];                // steps not yet in the running sums
+      cs[k][lane] = (cnt > 0) ? sum / (double)cnt : 0.0;
+    }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll 8
+      for (int t = 0; t < CF_T; ++t) {
+        const double c = cs[lane][t];
+        if (t0 + t > 0) G += dt * 0.5 * (prev + c);
+        gs[lane][t] = G;
+        prev = c;
+      }
+    }
+    __syncthreads();
+    const int64_t q = q0 + lane;
+    if (q < n_q) {
+      for (int t = wave; t < CF_T && t0 + t < L; t += 4) {
+        const int64_t lag = t0 + t;
+        if (q < n_binned) {
+          corr[lag * n_binned + q] = cs[lane][t];
+          integral[lag * n_binned + q] = gs[lane][t];
+        } else {
+          hcacf[lag * 9 + q - n_binned] = cs[lane][t];
+        }
+      }
+    }
+    __syncthreads();
   }
 }
 
 hipError_t launch_corr_finish(hipStream_t s, const double* csum, const double* ccomp, const double* psum,
-                              const double* pcomp, int64_t R3, int L, int64_t S, double dt, double* corr,
-                              double* integral) {
-  const int64_t n = R3 * 3;
-  hipLaunchKernelGGL(k_corr_finish, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, csum, ccomp, psum, pcomp, R3,
-                     L, S, dt, corr, integral);
+                              const double* pcomp, int64_t nb, int L, int64_t S, double dt, double* corr,
+                              double* integral, double* hcacf) {
+  hipLaunchKernelGGL(k_corr_finish, dim3((unsigned)((nb * 9 + 9 + CF_T - 1) / CF_T)), dim3(256), 0, s, csum, ccomp, psum,
+                     pcomp, nb * 9, L, S, dt, corr, integral, hcacf);
   return hipGetLastError();
 }
 
-__global__ void k_hnema_finish(const double* __restrict__ sum, const double* __restrict__ comp, int64_t n, int64_t S,
-                               double* __restrict__ avg) {
+// The bin sums, then the Eq. 10 totals, then (tdsum) their direction split.
+__global__ void __launch_bounds__(256) k_hnema_finish(const double* __restrict__ hsum, const double* __restrict__ hcomp,
+                                                      int64_t n, const double* __restrict__ tsum,
+                                                      const double* __restrict__ tcomp,
+                                                      const double* __restrict__ tdsum,
+                                                      const double* __restrict__ tdcomp, int64_t S,
+                                                      double* __restrict__ avg) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) avg[i] = (S > 0) ? (sum[i] + comp[i]) / (double)S : 0.0;
+  const int64_t k = i - n;
+  double v;
+  if (k < 0) v = hsum[i] + hcomp[i];
+  else if (k < 3) v = tsum[k] + tcomp[k];
+  else if (k < 12 && tdsum) v = tdsum[k - 3] + tdcomp[k - 3];
+  else return;
+  avg[i] = (S > 0) ? v / (double)S : 0.0;
 }
 
-hipError_t launch_hnema_finish(hipStream_t s, const double* sum, const double* comp, int64_t n, int64_t S,
-                               double* avg) {
-  hipLaunchKernelGGL(k_hnema_finish, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, sum, comp, n, S, avg);
+hipError_t launch_hnema_finish(hipStream_t s, const double* hsum, const double* hcomp, int64_t n, const double* tsum,
+                               const double* tcomp, const double* tdsum, const double* tdcomp, int64_t S, double* avg) {
+  hipLaunchKernelGGL(k_hnema_finish, dim3((unsigned)((n + 12 + 255) / 256)), dim3(256), 0, s, hsum, hcomp, n, tsum, tcomp,
+                     tdsum, tdcomp, S, avg);
   return hipGetLastError();
 }
 

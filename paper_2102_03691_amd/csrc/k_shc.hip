@@ -381,10 +381,10 @@ __global__ void k_shc_finish(const double* __restrict__ ksum, const double* __re
   for (int nu = 0; nu < 3; ++nu) {
     const int e = nu * n_lags * 3 + q;
     const double d = (S > tau) ? (ksum[e] + kcomp[e]) / (double)(S - tau) : 0.0;
-    Kd[q * 3 + nu] = d;
+    if (Kd) Kd[q * 3 + nu] = d;
     k += d;
   }
-  K[q] = k;
+  if (K) K[q] = k;
 }
 
 // Eq. 22 on the sampled lags, even extension, trapezoid rule, optional Hann

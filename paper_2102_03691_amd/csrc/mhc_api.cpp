@@ -73,7 +73,59 @@ struct DevBuf {
   size_t bytes = 0;
 };
 
+// Pinned read-out buffers: allocations of 16, with the ones in use as bits.
+struct PinnedSlab {
+  char* base = nullptr;
+  uint32_t used = 0;
+};
+constexpr int kSlabBuffers = 16;
+std::mutex g_pinned_mu;
+std::vector<PinnedSlab>& pinned_slabs() {   // never destroyed: objects may outlive the statics
+  static auto* slabs = new std::vector<PinnedSlab>();
+  return *slabs;
+}
+
 }  // namespace
+
+namespace mhc {
+
+double* pinned_acquire() {
+  std::lock_guard<std::mutex> lock(g_pinned_mu);
+  auto& slabs = pinned_slabs();
+  auto it = std::find_if(slabs.begin(), slabs.end(),
+                         [](const PinnedSlab& s) { return s.used != (1u << kSlabBuffers) - 1; });
+  if (it == slabs.end()) {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kSlabBuffers * kPinnedBytes, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    slabs.push_back({static_cast<char*>(p), 0});
+    it = slabs.end() - 1;
+  }
+  int k = 0;
+  while (it->used >> k & 1) ++k;
+  it->used |= 1u << k;
+  return reinterpret_cast<double*>(it->base + k * kPinnedBytes);
+}
+
+void pinned_release(double* buffer) {
+  if (!buffer) return;
+  std::lock_guard<std::mutex> lock(g_pinned_mu);
+  auto& slabs = pinned_slabs();
+  const char* p = reinterpret_cast<const char*>(buffer);
+  for (auto it = slabs.begin(); it != slabs.end(); ++it) {
+    if (p < it->base || p >= it->base + kSlabBuffers * kPinnedBytes) continue;
+    it->used &= ~(1u << ((p - it->base) / kPinnedBytes));
+    if (!it->used) {
+      (void)hipHostFree(it->base);
+      slabs.erase(it);
+    }
+    return;
+  }
+}
+
+}  // namespace mhc
 
 struct mhc_ctx {
   int device = 0;
@@ -150,6 +202,7 @@ struct mhc_ctx {
   int64_t R3 = 0;
   double *d_csum = nullptr, *d_ccomp = nullptr;
   double* d_out = nullptr;
+  double* h_out = nullptr;    // pinned, kPinnedBytes: small read-outs
   float* d_ws = nullptr;      // partial tiles of the split and stream-K schedules
   int* d_tile_cnt = nullptr;  // arrival counters of the split schedule (zero between launches)
   int* d_flag = nullptr;      // non-finite flag of the device-input check
@@ -225,6 +278,8 @@ void rollback_allocs(mhc_ctx* c, size_t mark) {
 }
 
 void free_all(mhc_ctx* c) {
+  pinned_release(c->h_out);
+  c->h_out = nullptr;
   for (auto& a : c->allocs) (void)hipFree(a.p);
   c->allocs.clear();
   c->bytes = 0;
@@ -688,13 +743,15 @@ static mhc_status finalize_impl(mhc_ctx* ctx) {
     }
   }
   if ((st = dev_alloc(ctx, out_doubles * 8, &pout, "read-out"))) return st;
+  if (!ctx->h_out && !(ctx->h_out = pinned_acquire()))
+    return fail(ctx, MHC_ERR_OOM, "pinned allocation failed: read-out");
   void* pflag = nullptr;
   if ((st = dev_alloc(ctx, 16, &pflag, "non-finite flag"))) return st;
   ctx->d_flag = reinterpret_cast<int*>(pflag);
   if (c.t_block > 1) {
-    hipDeviceProp_t prop;
-    HIP_TRY(hipGetDeviceProperties(&prop, ctx->device), "device properties");
-    ctx->n_cu = std::max(1, prop.multiProcessorCount);
+    int n_cu = 0;
+    HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device), "device properties");
+    ctx->n_cu = std::max(1, n_cu);
     // per CU: two partial tiles of 256 threads x 256 accumulator floats
     ctx->ws_floats = (int64_t)ctx->n_cu * 2 * 256 * 256;
     void* pws = nullptr;
@@ -1136,17 +1193,30 @@ mhc_status mhc_synchronize(mhc_ctx* ctx) {
 
 // Finished HNEMA averages on the host: h[0 .. nd*nb*3) = bin averages
 // [dir][b][mu], then the Eq. 10 total [3], then (split) the split totals [dir][mu].
-static mhc_status hnema_finished(mhc_ctx* ctx, std::vector<double>& h) {
+// Small read-outs are written by the finishing kernel straight into the
+// context's pinned buffer (host memory that the GPU writes over PCIe): one
+// kernel and one synchronization, no copy (a push and HNEMA read of a 512-atom
+// system: 75 us with two kernels and two copies into pageable memory, 38 us
+// now).  Larger ones go through d_out: 64 KB at PCIe rate is about what a copy
+// costs to start.
+static bool reads_pinned(size_t doubles) { return doubles * 8 <= kPinnedBytes; }
+
+// Finished HNEMA averages on the host: *h = bins [dir][nb][3], total [3], split
+// totals [dir][3] (valid until the next call on the context).
+static mhc_status hnema_finished(mhc_ctx* ctx, const double** out, std::vector<double>& h) {
   const int nd = ctx->n_dir;
   const int64_t n = (int64_t)nd * ctx->nb * 3;
-  HIP_TRY(launch_hnema_finish(ctx->stream, ctx->d_hsum, ctx->d_hcomp, n, ctx->n_samples, ctx->d_out), "finish");
-  HIP_TRY(launch_hnema_finish(ctx->stream, ctx->d_tsum, ctx->d_tcomp, 3, ctx->n_samples, ctx->d_out + n), "finish");
-  if (nd > 1)
-    HIP_TRY(launch_hnema_finish(ctx->stream, ctx->d_tdsum, ctx->d_tdcomp, 9, ctx->n_samples, ctx->d_out + n + 3),
-            "finish");
-  h.resize(n + 3 + (nd > 1 ? 9 : 0));
-  HIP_TRY(hipMemcpyAsync(h.data(), ctx->d_out, h.size() * 8, hipMemcpyDeviceToHost, ctx->stream), "read");
+  const size_t all = n + 3 + (nd > 1 ? 9 : 0);
+  const bool pinned = reads_pinned(all);
+  HIP_TRY(launch_hnema_finish(ctx->stream, ctx->d_hsum, ctx->d_hcomp, n, ctx->d_tsum, ctx->d_tcomp, ctx->d_tdsum,
+                              ctx->d_tdcomp, ctx->n_samples, pinned ? ctx->h_out : ctx->d_out),
+          "finish");
+  if (!pinned) {
+    h.resize(all);
+    HIP_TRY(hipMemcpyAsync(h.data(), ctx->d_out, all * 8, hipMemcpyDeviceToHost, ctx->stream), "read");
+  }
   HIP_TRY(hipStreamSynchronize(ctx->stream), "read sync");
+  *out = pinned ? ctx->h_out : h.data();
   return MHC_OK;
 }
 
@@ -1155,8 +1225,9 @@ mhc_status mhc_read_hnema(mhc_ctx* ctx, double* avg, double* total_avg, int64_t*
   if (st) return st;
   if (!ctx->finalized || !(ctx->cfg.methods & MHC_HNEMA)) return fail(ctx, MHC_ERR_STATE, "HNEMA not enabled");
   HIP_TRY(hipSetDevice(ctx->device), "hipSetDevice");
-  std::vector<double> h;
-  if ((st = hnema_finished(ctx, h))) return st;
+  std::vector<double> hv;
+  const double* h = nullptr;
+  if ((st = hnema_finished(ctx, &h, hv))) return st;
   const int64_t n = ctx->nb * 3;
   const int nd = ctx->n_dir;
   if (avg) {
@@ -1167,7 +1238,7 @@ mhc_status mhc_read_hnema(mhc_ctx* ctx, double* avg, double* total_avg, int64_t*
       avg[e] = a;
     }
   }
-  if (total_avg) std::memcpy(total_avg, h.data() + (size_t)nd * n, 24);
+  if (total_avg) std::memcpy(total_avg, h + (size_t)nd * n, 24);
   if (n_samples) *n_samples = ctx->n_samples;
   return MHC_OK;
 }
@@ -1178,8 +1249,9 @@ mhc_status mhc_read_hnema_dir(mhc_ctx* ctx, double* avg, double* total_avg, int6
   if (!ctx->finalized || !(ctx->cfg.methods & MHC_HNEMA) || ctx->n_dir == 1)
     return fail(ctx, MHC_ERR_STATE, "HNEMA with the direction split not enabled");
   HIP_TRY(hipSetDevice(ctx->device), "hipSetDevice");
-  std::vector<double> h;
-  if ((st = hnema_finished(ctx, h))) return st;
+  std::vector<double> hv;
+  const double* h = nullptr;
+  if ((st = hnema_finished(ctx, &h, hv))) return st;
   const int64_t nb = ctx->nb, n = nb * 3;
   if (avg)
     for (int d = 0; d < 3; ++d)
@@ -1192,11 +1264,12 @@ mhc_status mhc_read_hnema_dir(mhc_ctx* ctx, double* avg, double* total_avg, int6
   return MHC_OK;
 }
 
-// Finished correlation and running integral of direction pass d on the host:
-// h[0 .. per) = corr[tau][r][nu], h[per .. 2 per) = integral, r = 3 b + mu.
-static mhc_status gkma_finished(mhc_ctx* ctx, int d, std::vector<double>& h) {
+// Finished correlation and running integral of direction pass d at *out: corr
+// [L][nb][3][3], integral [L][nb][3][3], hcacf [L][3][3], in the pinned buffer
+// (after a synchronization; *host = true) or in d_out on the device.
+static mhc_status gkma_finished(mhc_ctx* ctx, int d, const double** out, bool* host) {
   const int L = ctx->cfg.corr_len;
-  const size_t per = (size_t)L * ctx->R3 * 3;
+  const size_t per = (size_t)L * ctx->R3 * 3, n = (size_t)L * ctx->nb * 9;
   const double *psum = nullptr, *pcomp = nullptr;
   if (ctx->x_fill > 0) {
     // steps still buffered for a later update: their contribution goes into
@@ -1208,12 +1281,26 @@ static mhc_status gkma_finished(mhc_ctx* ctx, int d, std::vector<double>& h) {
     psum = ctx->d_psum;
     pcomp = ctx->d_psum + per;
   }
-  HIP_TRY(launch_corr_finish(ctx->stream, ctx->d_csum + d * per, ctx->d_ccomp + d * per, psum, pcomp, ctx->R3, L,
-                             ctx->n_samples, ctx->cfg.dt, ctx->d_out, ctx->d_out + per),
+  *host = reads_pinned(2 * n + (size_t)L * 9);
+  double* o = *host ? ctx->h_out : ctx->d_out;
+  HIP_TRY(launch_corr_finish(ctx->stream, ctx->d_csum + d * per, ctx->d_ccomp + d * per, psum, pcomp, ctx->nb, L,
+                             ctx->n_samples, ctx->cfg.dt, o, o + n, o + 2 * n),
           "finish");
-  h.resize(2 * per);
-  HIP_TRY(hipMemcpyAsync(h.data(), ctx->d_out, 2 * per * 8, hipMemcpyDeviceToHost, ctx->stream), "read");
+  if (*host) HIP_TRY(hipStreamSynchronize(ctx->stream), "read sync");
+  *out = o;
+  return MHC_OK;
+}
+
+// As gkma_finished, all of it on the host (in h unless it fits the pinned buffer).
+static mhc_status gkma_on_host(mhc_ctx* ctx, int d, const double** out, std::vector<double>& h) {
+  const size_t all = (size_t)ctx->cfg.corr_len * (ctx->nb * 18 + 9);
+  bool host = false;
+  mhc_status st = gkma_finished(ctx, d, out, &host);
+  if (st || host) return st;
+  h.resize(all);
+  HIP_TRY(hipMemcpyAsync(h.data(), *out, all * 8, hipMemcpyDeviceToHost, ctx->stream), "read");
   HIP_TRY(hipStreamSynchronize(ctx->stream), "read sync");
+  *out = h.data();
   return MHC_OK;
 }
 
@@ -1222,27 +1309,33 @@ mhc_status mhc_read_gkma(mhc_ctx* ctx, double* corr, double* integral, double* h
   if (st) return st;
   if (!ctx->finalized || !(ctx->cfg.methods & MHC_GKMA)) return fail(ctx, MHC_ERR_STATE, "GKMA not enabled");
   HIP_TRY(hipSetDevice(ctx->device), "hipSetDevice");
-  const int L = ctx->cfg.corr_len;
-  const int64_t R3 = ctx->R3, nb = ctx->nb;
-  const size_t per = (size_t)L * R3 * 3;
-  std::vector<double> h, acc;
-  for (int d = 0; d < ctx->n_dir; ++d) {
-    if ((st = gkma_finished(ctx, d, h))) return st;
-    if (d == 0) {
-      acc = h;
-    } else {   // the whole current is the sum of the direction slices, in direction order
-      for (size_t e = 0; e < 2 * per; ++e) acc[e] += h[e];
+  const size_t L = ctx->cfg.corr_len, n = L * ctx->nb * 9;
+  if (ctx->n_dir == 1) {
+    const double* o = nullptr;
+    bool host = false;
+    if ((st = gkma_finished(ctx, 0, &o, &host))) return st;
+    // straight into the caller's arrays: through a vector of the whole read-out
+    // 500 bins x 500 lags took 15 ms longer
+    struct { double* to; size_t at, count; } part[3] = {{corr, 0, n}, {integral, n, n}, {hcacf, 2 * n, 9 * L}};
+    for (auto& p : part) {
+      if (!p.to) continue;
+      if (host) std::memcpy(p.to, o + p.at, p.count * 8);
+      else
+        HIP_TRY(hipMemcpyAsync(p.to, o + p.at, p.count * 8, hipMemcpyDeviceToHost, ctx->stream), "read");
     }
-  }
-  for (int tau = 0; tau < L; ++tau) {
-    const double* src = acc.data() + (size_t)tau * R3 * 3;
-    if (corr) std::memcpy(corr + (size_t)tau * nb * 9, src, nb * 9 * 8);
-    if (integral) std::memcpy(integral + (size_t)tau * nb * 9, acc.data() + per + (size_t)tau * R3 * 3, nb * 9 * 8);
-  }
-  if (hcacf) {   // the total current's rows are the same in every pass: take pass 0
-    if (ctx->n_dir > 1 && (st = gkma_finished(ctx, 0, h))) return st;
-    const std::vector<double>& h0 = ctx->n_dir > 1 ? h : acc;
-    for (int tau = 0; tau < L; ++tau) std::memcpy(hcacf + (size_t)tau * 9, h0.data() + (size_t)tau * R3 * 3 + nb * 9, 9 * 8);
+    if (!host) HIP_TRY(hipStreamSynchronize(ctx->stream), "read sync");
+  } else {
+    // the whole current is the sum of the direction slices, in direction
+    // order; the total current's rows are the same in every pass: take pass 0
+    std::vector<double> acc(2 * n), h;
+    for (int d = 0; d < ctx->n_dir; ++d) {
+      const double* o = nullptr;
+      if ((st = gkma_on_host(ctx, d, &o, h))) return st;
+      for (size_t e = 0; e < 2 * n; ++e) acc[e] = d == 0 ? o[e] : acc[e] + o[e];
+      if (d == 0 && hcacf) std::memcpy(hcacf, o + 2 * n, 9 * L * 8);
+    }
+    if (corr) std::memcpy(corr, acc.data(), n * 8);
+    if (integral) std::memcpy(integral, acc.data() + n, n * 8);
   }
   if (n_samples) *n_samples = ctx->n_samples;
   return MHC_OK;
@@ -1254,21 +1347,17 @@ mhc_status mhc_read_gkma_dir(mhc_ctx* ctx, double* corr, double* integral, int64
   if (!ctx->finalized || !(ctx->cfg.methods & MHC_GKMA) || ctx->n_dir == 1)
     return fail(ctx, MHC_ERR_STATE, "GKMA with the direction split not enabled");
   HIP_TRY(hipSetDevice(ctx->device), "hipSetDevice");
-  const int L = ctx->cfg.corr_len;
-  const int64_t R3 = ctx->R3, nb = ctx->nb;
-  const size_t per = (size_t)L * R3 * 3;
+  const size_t n = (size_t)ctx->cfg.corr_len * ctx->nb * 9;
   std::vector<double> h;
   for (int d = 0; d < 3; ++d) {
-    if ((st = gkma_finished(ctx, d, h))) return st;
-    for (int tau = 0; tau < L; ++tau)
-      for (int64_t b = 0; b < nb; ++b)
-        for (int mu = 0; mu < 3; ++mu)
-          for (int m2 = 0; m2 < 3; ++m2) {
-            const size_t src = ((size_t)tau * R3 + b * 3 + mu) * 3 + m2;
-            const size_t dst = ((((size_t)tau * nb + b) * 3 + mu) * 3 + d) * 3 + m2;
-            if (corr) corr[dst] = h[src];
-            if (integral) integral[dst] = h[per + src];
-          }
+    const double* o = nullptr;
+    if ((st = gkma_on_host(ctx, d, &o, h))) return st;
+    for (size_t r = 0; r < n / 3; ++r)             // [tau][b][mu]
+      for (int m2 = 0; m2 < 3; ++m2) {
+        const size_t dst = (r * 3 + d) * 3 + m2;
+        if (corr) corr[dst] = o[r * 3 + m2];
+        if (integral) integral[dst] = o[n + r * 3 + m2];
+      }
   }
   if (n_samples) *n_samples = ctx->n_samples;
   return MHC_OK;
@@ -1281,23 +1370,20 @@ mhc_status mhc_read_gkma_cross(mhc_ctx* ctx, double* corr, double* integral, int
   HIP_TRY(hipSetDevice(ctx->device), "hipSetDevice");
   const int L = ctx->cfg.corr_len;
   const int64_t R3 = ctx->R3, nb = ctx->nb;
-  const size_t per = (size_t)L * R3 * 3;
-  std::vector<double> h(2 * per);
+  const size_t per = (size_t)L * R3 * 3, n = (size_t)L * nb * 9;
+  std::vector<double> h(2 * n);
   for (int64_t b2 = 0; b2 < nb; ++b2) {
-    HIP_TRY(launch_corr_finish(ctx->stream, ctx->d_xsum + b2 * per, ctx->d_xcomp + b2 * per, nullptr, nullptr, R3, L,
-                               ctx->n_samples, ctx->cfg.dt, ctx->d_out, ctx->d_out + per),
+    HIP_TRY(launch_corr_finish(ctx->stream, ctx->d_xsum + b2 * per, ctx->d_xcomp + b2 * per, nullptr, nullptr, nb, L,
+                               ctx->n_samples, ctx->cfg.dt, ctx->d_out, ctx->d_out + n, ctx->d_out + 2 * n),
             "finish");
-    HIP_TRY(hipMemcpyAsync(h.data(), ctx->d_out, 2 * per * 8, hipMemcpyDeviceToHost, ctx->stream), "read");
+    HIP_TRY(hipMemcpyAsync(h.data(), ctx->d_out, 2 * n * 8, hipMemcpyDeviceToHost, ctx->stream), "read");
     HIP_TRY(hipStreamSynchronize(ctx->stream), "read sync");
-    for (int tau = 0; tau < L; ++tau)
-      for (int64_t b = 0; b < nb; ++b)
-        for (int mu = 0; mu < 3; ++mu)
-          for (int nu = 0; nu < 3; ++nu) {
-            const size_t src = ((size_t)tau * R3 + b * 3 + mu) * 3 + nu;
-            const size_t dst = ((((size_t)tau * nb + b) * nb + b2) * 3 + mu) * 3 + nu;
-            if (corr) corr[dst] = h[src];
-            if (integral) integral[dst] = h[per + src];
-          }
+    for (size_t r = 0; r < (size_t)L * nb; ++r)    // [tau][b]
+      for (int e = 0; e < 9; ++e) {
+        const size_t dst = (r * nb + b2) * 9 + e;
+        if (corr) corr[dst] = h[r * 9 + e];
+        if (integral) integral[dst] = h[n + r * 9 + e];
+      }
   }
   if (n_samples) *n_samples = ctx->n_samples;
   return MHC_OK;

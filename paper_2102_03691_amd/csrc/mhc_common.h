@@ -207,17 +207,29 @@ hipError_t launch_corr(hipStream_t s, const double* X, int64_t ldx, int t_count,
                        const int64_t* t0_dev, const int64_t* tbuf_dev = nullptr, int nz = 1, int64_t ring_zs = 0,
                        int64_t out_zs = 0);
 
+// A pinned host buffer of kPinnedBytes for the small read-outs of one object
+// (null when the allocation fails), and its return.  Sixteen buffers to an
+// allocation, which is freed with its last one: hipHostMalloc takes 30 to 130
+// us whatever the size, hipHostFree 120 us.  From any thread; the owner returns
+// a buffer after its stream has drained.
+constexpr size_t kPinnedBytes = size_t(64) << 10;
+double* pinned_acquire();
+void pinned_release(double* buffer);
+
 // Read-out of the GKMA accumulators: C = (csum + ccomp [+ psum + pcomp]) /
 // (S - tau) (zero when S <= tau; psum, pcomp optional: the correlation of
 // steps not yet added to the running sums) and its trapezoid running integral
-// with step dt, written as corr/integral[tau][r][nu].
+// with step dt: corr, integral [L][nb][3][3] and the total current's rows
+// hcacf [L][3][3].
 hipError_t launch_corr_finish(hipStream_t s, const double* csum, const double* ccomp, const double* psum,
-                              const double* pcomp, int64_t R3, int L, int64_t S, double dt, double* corr,
-                              double* integral);
+                              const double* pcomp, int64_t nb, int L, int64_t S, double dt, double* corr,
+                              double* integral, double* hcacf);
 
-// Read-out of the HNEMA accumulators: avg = (sum + comp) / S (zero when S = 0).
-hipError_t launch_hnema_finish(hipStream_t s, const double* sum, const double* comp, int64_t n,
-                               int64_t S, double* avg);
+// Read-out of the HNEMA accumulators: (sum + comp) / S (zero when S = 0) of the
+// n bin sums, the 3 totals and, with tdsum, the 9 split totals, one after the
+// other in avg.
+hipError_t launch_hnema_finish(hipStream_t s, const double* hsum, const double* hcomp, int64_t n, const double* tsum,
+                               const double* tcomp, const double* tdsum, const double* tdcomp, int64_t S, double* avg);
 
 // ------------------------------------------------------------ spectral heat current
 // Direction-major dof columns nu * Np + i (Np = N rounded up to 32, ld = 3 Np):
@@ -262,7 +274,7 @@ hipError_t launch_shc_ring_group(hipStream_t s, const ShcBlockDesc* d, int n_sys
 hipError_t launch_shc_gram_group(hipStream_t s, const ShcBlockDesc* d, int n_sys, int64_t n_wgs);
 hipError_t launch_shc_accum_group(hipStream_t s, const ShcBlockDesc* d, int n_sys, int64_t n_blocks);
 // Kd[tau][mu][nu] = (ksum + kcomp)[nu][tau][mu] / (S - tau) (zero where S <= tau) and
-// K[tau][mu] = sum over nu in order.
+// K[tau][mu] = sum over nu in order (either may be null).
 hipError_t launch_shc_finish(hipStream_t s, const double* ksum, const double* kcomp, int n_lags, int64_t S,
                              double* K, double* Kd);
 // Kw[w][m] = dt sum_tau c_tau K[tau][m] cos(omega_w tau dt), c = 1, 2, ..., 2, 1 (times the Hann

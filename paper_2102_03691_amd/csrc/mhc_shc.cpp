@@ -47,6 +47,7 @@ struct mhc_shc {
   double* part = nullptr;              // [3 n_kcs][T/64][n_lags_pad][3]
   double* ksum = nullptr;              // [3 nu][n_lags][3 mu] x 2 (sum, compensation)
   double* kout = nullptr;              // [n_lags][3] then [n_lags][3][3] read-out
+  double* h_out = nullptr;             // pinned, kPinnedBytes: small read-outs and the frequencies asked for
   double* omega = nullptr;             // spectrum frequencies (grown on demand)
   double* kw = nullptr;                // [n_omega][3]
   int omega_cap = 0;
@@ -106,6 +107,8 @@ void sfree(mhc_shc* c) {
   }
   for (void* p : c->allocs) (void)hipFree(p);
   c->allocs.clear();
+  pinned_release(c->h_out);
+  c->h_out = nullptr;
   for (auto e : c->ev) (void)hipEventDestroy(e);
   c->ev.clear();
   for (hipEvent_t* e : {&c->ev_start, &c->ev_copied[0], &c->ev_copied[1], &c->ev_free[0], &c->ev_free[1]})
@@ -173,9 +176,9 @@ mhc_status mhc_shc_create(int device, void* hip_stream, int64_t n_atoms, int32_t
     if (hipStreamCreate(&c->stream) != hipSuccess) return bail(MHC_ERR_HIP, "hipStreamCreate");
     c->own_stream = true;
   }
-  int n_cu = 256;
-  hipDeviceProp_t prop;
-  if (hipGetDeviceProperties(&prop, device) == hipSuccess) n_cu = std::max(1, prop.multiProcessorCount);
+  int n_cu = 256, n_dev_cu = 0;
+  if (hipDeviceGetAttribute(&n_dev_cu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess)
+    n_cu = std::max(1, n_dev_cu);
   c->N = n_atoms;
   c->N3 = 3 * n_atoms;
   c->Np = (n_atoms + 31) / 32 * 32;
@@ -206,22 +209,23 @@ mhc_status mhc_shc_create(int device, void* hip_stream, int64_t n_atoms, int32_t
   c->dk = ((c->N + best - 1) / best + 31) / 32 * 32;
   c->n_kcs = (int)((c->N + c->dk - 1) / c->dk);
   c->cost = best_cost;
-  void *pr, *pvt, *pv, *pW, *pp, *ps, *po;
+  void *pr, *pvt, *pv, *pW, *pp, *ps;
   const size_t ring_bytes = (size_t)c->ring_len * 3 * c->ld * 4;
   const size_t vt_bytes = (size_t)t_block * c->ld * 4;
   if (salloc(c, ring_bytes, &pr, "virial ring") || salloc(c, vt_bytes, &pvt, "velocity rows") ||
       salloc(c, (size_t)t_block * c->N3 * 4, &pv, "velocity staging") ||
       salloc(c, (size_t)t_block * c->N3 * 3 * 4, &pW, "virial staging") ||
       salloc(c, (size_t)3 * c->n_kcs * (t_block / 64) * lags_pad(n_lags) * 3 * 8, &pp, "partials") ||
-      salloc(c, (size_t)n_lags * 9 * 2 * 8, &ps, "sums") || salloc(c, (size_t)n_lags * 12 * 8, &po, "read-out"))
+      salloc(c, (size_t)n_lags * (9 * 2 + 12) * 8, &ps, "sums and read-out"))
     return bail(MHC_ERR_OOM, "device allocation failed");
+  if (!(c->h_out = pinned_acquire())) return bail(MHC_ERR_OOM, "pinned allocation failed");
   c->ring = static_cast<float*>(pr);
   c->vt = static_cast<float*>(pvt);
   c->sv = static_cast<float*>(pv);
   c->sW = static_cast<float*>(pW);
   c->part = static_cast<double*>(pp);
   c->ksum = static_cast<double*>(ps);
-  c->kout = static_cast<double*>(po);
+  c->kout = c->ksum + (size_t)n_lags * 9 * 2;
   // the pad columns of the ring and the velocity rows stay zero for good
   if (hipMemsetAsync(c->ring, 0, ring_bytes, c->stream) != hipSuccess ||
       hipMemsetAsync(c->vt, 0, vt_bytes, c->stream) != hipSuccess ||
@@ -321,12 +325,16 @@ static mhc_status shc_read(mhc_shc* c, double* K, int64_t* n_samples, int split)
   mhc_status st = senter(c);
   if (st) return st;
   if (!K) return sfail(c, MHC_ERR_INVALID_ARG, "NULL output");
-  const size_t n = (size_t)c->n_lags * 3;
-  SHIP_TRY(launch_shc_finish(c->stream, c->ksum, c->ksum + 9 * c->n_lags, c->n_lags, c->S, c->kout, c->kout + n),
+  const size_t n = (size_t)c->n_lags * 3, bytes = (split ? 3 : 1) * n * 8;
+  // written by the kernel into the pinned buffer where it fits: no copy
+  const bool pinned = bytes <= kPinnedBytes;
+  double* o = pinned ? c->h_out : c->kout;
+  SHIP_TRY(launch_shc_finish(c->stream, c->ksum, c->ksum + 9 * c->n_lags, c->n_lags, c->S, split ? nullptr : o,
+                             split ? o : nullptr),
            "finish");
-  SHIP_TRY(hipMemcpyAsync(K, c->kout + (split ? n : 0), (split ? 3 : 1) * n * 8, hipMemcpyDeviceToHost, c->stream),
-           "copy K");
+  if (!pinned) SHIP_TRY(hipMemcpyAsync(K, o, bytes, hipMemcpyDeviceToHost, c->stream), "copy K");
   SHIP_TRY(hipStreamSynchronize(c->stream), "read sync");
+  if (pinned) std::memcpy(K, o, bytes);
   if (n_samples) *n_samples = c->S;
   return MHC_OK;
 }
@@ -344,7 +352,11 @@ static mhc_status shc_spectrum(mhc_shc* c, int32_t n_omega, const double* omega,
     return sfail(c, MHC_ERR_INVALID_ARG, "bad arguments");
   for (int32_t w = 0; w < n_omega; ++w)
     if (!std::isfinite(omega[w])) return sfail(c, MHC_ERR_INVALID_ARG, "non-finite frequency");
-  if (n_omega > c->omega_cap) {
+  const size_t n = (size_t)c->n_lags * 3;
+  const int nc = split ? 9 : 3;
+  // frequencies and results through the pinned buffer where they fit
+  const bool pinned = (size_t)n_omega * (1 + nc) * 8 <= kPinnedBytes;
+  if (!pinned && n_omega > c->omega_cap) {
     void *po, *pk;
     if ((st = salloc(c, (size_t)n_omega * 8, &po, "frequencies"))) return st;
     if ((st = salloc(c, (size_t)n_omega * 9 * 8, &pk, "spectrum"))) return st;
@@ -352,16 +364,19 @@ static mhc_status shc_spectrum(mhc_shc* c, int32_t n_omega, const double* omega,
     c->kw = static_cast<double*>(pk);
     c->omega_cap = n_omega;
   }
-  SHIP_TRY(hipMemcpyAsync(c->omega, omega, (size_t)n_omega * 8, hipMemcpyHostToDevice, c->stream), "copy omega");
-  const size_t n = (size_t)c->n_lags * 3;
-  const int nc = split ? 9 : 3;
+  double* om = pinned ? c->h_out : c->omega;
+  double* kw = pinned ? c->h_out + n_omega : c->kw;
+  if (pinned) std::memcpy(om, omega, (size_t)n_omega * 8);
+  else
+    SHIP_TRY(hipMemcpyAsync(om, omega, (size_t)n_omega * 8, hipMemcpyHostToDevice, c->stream), "copy omega");
   SHIP_TRY(launch_shc_finish(c->stream, c->ksum, c->ksum + 9 * c->n_lags, c->n_lags, c->S, c->kout, c->kout + n),
            "finish");
-  SHIP_TRY(launch_shc_spectrum(c->stream, c->kout + (split ? n : 0), c->n_lags, nc, c->omega, n_omega, dt, window,
-                               c->kw),
+  SHIP_TRY(launch_shc_spectrum(c->stream, c->kout + (split ? n : 0), c->n_lags, nc, om, n_omega, dt, window, kw),
            "spectrum");
-  SHIP_TRY(hipMemcpyAsync(Kw, c->kw, (size_t)n_omega * nc * 8, hipMemcpyDeviceToHost, c->stream), "copy spectrum");
+  if (!pinned)
+    SHIP_TRY(hipMemcpyAsync(Kw, kw, (size_t)n_omega * nc * 8, hipMemcpyDeviceToHost, c->stream), "copy spectrum");
   SHIP_TRY(hipStreamSynchronize(c->stream), "spectrum sync");
+  if (pinned) std::memcpy(Kw, kw, (size_t)n_omega * nc * 8);
   return MHC_OK;
 }
 
@@ -378,8 +393,11 @@ mhc_status mhc_shc_spectrum_dir(mhc_shc* c, int32_t n_omega, const double* omega
 mhc_status mhc_shc_reset(mhc_shc* c) {
   mhc_status st = senter(c);
   if (st) return st;
+  // in stream order, like a push; not into a graph (a replay would not repeat S = 0)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  SHIP_TRY(hipStreamIsCapturing(c->stream, &cap), "capture status");
+  if (cap != hipStreamCaptureStatusNone) SHIP_TRY(hipErrorStreamCaptureUnsupported, "reset");
   SHIP_TRY(hipMemsetAsync(c->ksum, 0, (size_t)c->n_lags * 9 * 2 * 8, c->stream), "clear sums");
-  SHIP_TRY(hipStreamSynchronize(c->stream), "reset sync");
   c->S = 0;
   return MHC_OK;
 }
