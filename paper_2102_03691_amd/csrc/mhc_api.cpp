@@ -682,7 +682,7 @@ static mhc_status finalize_impl(mhc_ctx* ctx) {
     void *pjd, *pjdt;
     const size_t jd_bytes = (size_t)(ctx->n3 ? 3 : 1) * t_pad * n_ac * 3 * 8;   // [nu][t][chunk][mu]
     if ((st = dev_alloc(ctx, jd_bytes, &pjd, "split total partials"))) return st;
-    if ((st = dev_alloc(ctx, (size_t)t_pad * 3 * 8, &pjdt, "split total current"))) return st;
+    if ((st = dev_alloc(ctx, (size_t)(ctx->n3 ? 3 : 1) * t_pad * 3 * 8, &pjdt, "split total current"))) return st;
     HIP_TRY(hipMemsetAsync(pjd, 0, jd_bytes, ctx->stream), "zero split partials");
     ctx->d_jd = reinterpret_cast<double*>(pjd);
     ctx->d_jdtot = reinterpret_cast<double*>(pjdt);
@@ -890,11 +890,22 @@ static mhc_status block_back(mhc_ctx* ctx, int t_count, int n_parts, int n_sub, 
   // the one-contraction split leaves every direction's currents and split
   // partials in their own regions; the pass-per-direction form reuses one
   const bool one = ctx->n3 > 0 && dir >= 0;
-  HIP_TRY(launch_total(ctx->stream, ctx->d_jt, ctx->n_atom_chunks, t_count, ctx->d_jtot), "total current");
-  if (dir >= 0 && ctx->d_tdsum)
-    HIP_TRY(launch_total(ctx->stream, ctx->d_jd + (one ? (int64_t)d * ctx->t_pad * ctx->n_atom_chunks * 3 : 0),
-                         ctx->n_atom_chunks, t_count, ctx->d_jdtot),
-            "split total current");
+  // one launch per kernel then serves the three directions, save the GKMA
+  // bin sums (X holds one direction's block at a time)
+  if (one && !gk && d > 0) return MHC_OK;
+  TotalArgs tot{};
+  tot.n_chunks = ctx->n_atom_chunks;
+  if (!one || d == 0) {
+    tot.jt_part = ctx->d_jt;
+    tot.jtot = ctx->d_jtot;
+    if (dir >= 0 && ctx->d_tdsum) {
+      tot.jd_part = ctx->d_jd;
+      tot.jdtot = ctx->d_jdtot;
+      tot.n_dir = one ? 3 : 1;
+      tot.jd_region = (int64_t)ctx->t_pad * ctx->n_atom_chunks * 3;
+      tot.jdtot_region = ctx->t_pad * 3;
+    }
+  }
   ReduceArgs a{};
   a.in = ctx->dJ + (one ? d * ctx->j_region : 0);
   a.layout_g = gk ? 1 : 0;
@@ -918,10 +929,13 @@ static mhc_status block_back(mhc_ctx* ctx, int t_count, int n_parts, int n_sub, 
   a.tsum = d == 0 ? ctx->d_tsum : nullptr;
   a.tcomp = d == 0 ? ctx->d_tcomp : nullptr;
   if (dir >= 0 && ctx->d_tdsum) {
-    a.jdtot = ctx->d_jdtot;
+    a.jdtot = ctx->d_jdtot + (one ? (int64_t)d * ctx->t_pad * 3 : 0);
     a.tdsum = ctx->d_tdsum + 3 * dir;
     a.tdcomp = ctx->d_tdcomp + 3 * dir;
   }
+  a.n_dir = one && !gk ? 3 : 1;
+  a.in_region = ctx->j_region;
+  a.jdtot_region = ctx->t_pad * 3;
   a.X = gk ? ctx->dX : nullptr;
   a.bring = ctx->d_bring;
   a.ring = ctx->d_ring;
@@ -933,7 +947,7 @@ static mhc_status block_back(mhc_ctx* ctx, int t_count, int n_parts, int n_sub, 
   if (gk && dir < 0 && !t0_dev) fold_step(ctx, t_count, &xoff, &tbuf);
   a.xoff = xoff;
   a.xoff_dev = t0_dev ? xoff_dev : nullptr;
-  HIP_TRY(launch_reduce(ctx->stream, a), "bin reduce");
+  HIP_TRY(launch_reduce(ctx->stream, a, tot), "bin reduce");
   if (!gk) return MHC_OK;
   if (dir >= 0) {
     // direction passes: one update per pass over this block (X holds one block)

@@ -176,7 +176,7 @@ struct ReduceArgs {
   const float* in; int layout_g; int n_parts; int n_sub; int64_t M_pad; int64_t ld; int t_count;
   const int32_t* bin_off; int nb;
   const int32_t* slot_bin; double* seg_part; int n_seg;      // GKMA segment pass
-  const double* jtot;
+  double* jtot;
   double* hsum; double* hcomp; double* tsum; double* tcomp;  // HNEMA (may be null)
   double* X;                                                 // GKMA (may be null)
   double* ring; int64_t ring_len; int64_t t0;                // GKMA history
@@ -187,11 +187,21 @@ struct ReduceArgs {
   int64_t xoff;             // column of X where this block's first step goes
   const int64_t* xoff_dev;  // if set, xoff is read here (the group's block table)
   double* slot_sum;         // HNEMA-only, n_sub = 1: if set, the parts are first summed per (slot, mu) into it [M_pad][3]
+  const double* jt_part; int n_chunks;   // if set, jtot is summed from the atom chunks' partials on the way
+  int n_dir; int64_t in_region, jdtot_region;   // one-contraction split, HNEMA only: count and strides of the direction
+                                                // regions of in and jdtot (hsum, tdsum: [dir][nb][3], [dir][3]); else 1
 };
-hipError_t launch_reduce(hipStream_t s, const ReduceArgs& a);
 
-// Per-step total current: jtot[t][mu] = sum over atom chunks of jt_part[t][chunk][mu].
-hipError_t launch_total(hipStream_t s, const double* jt_part, int n_chunks, int t_count, double* jtot);
+// Per-step total currents: jtot[t][mu] = sum over atom chunks of
+// jt_part[t][chunk][mu], and the same for n_dir regions of split partials.
+struct TotalArgs {
+  const double* jt_part; int n_chunks; double* jtot;
+  const double* jd_part; double* jdtot; int64_t jd_region, jdtot_region; int n_dir;
+};
+
+// Bin sums of a block, with the totals of tot first (no totals if its jt_part
+// is null), over a.n_dir >= 1 direction regions.
+hipError_t launch_reduce(hipStream_t s, ReduceArgs a, const TotalArgs& tot);
 
 // GKMA correlation update: for r < R3 = 3(nb+1), tau < L, nu < 3
 //   C[r][nu][tau] += sum_{t < t_count, t0+t-tau >= 0} X[r][t] * ring[(t0+t-tau) % ring_len][nu]

@@ -24,7 +24,8 @@ def _gpu():
         pytest.skip("no GPU")
 
 
-@pytest.mark.parametrize("nb,L,S", [(6, 2, 5), (6, 63, 70), (7, 64, 70), (7, 65, 70), (13, 129, 40), (20, 200, 250)])
+@pytest.mark.parametrize("nb,L,S", [(6, 2, 5), (6, 63, 70), (7, 64, 70), (7, 65, 70), (13, 129, 40), (20, 200, 250),
+                                      (1500, 960, 70)])     # the last: correlation tiles of 64 lags
 def test_gkma_finish_tiles(nb, L, S):
     announce(f"gkma read-out nb={nb} L={L} S={S}")
     case = Case((3, 3, 2), S, "natural", 5)
