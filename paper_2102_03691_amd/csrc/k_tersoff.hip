@@ -412,9 +412,10 @@ __device__ __forceinline__ void angle_fn(const TersoffParams& p, double cs, doub
   *dg = p.g2c2 * t * inv * inv;
 }
 
-// exp(l3^m x^m) and its derivative in x (m = 1 or 3)
+// exp(l3^m x^m) and its derivative in x (m = 1 or 3); L3 = false: lambda3 = 0
+template <bool L3>
 __device__ __forceinline__ void exp_fn(const TersoffParams& p, double x, double* e, double* de) {
-  if (p.l3m == 0.0) {
+  if (!L3) {
     *e = 1.0;
     *de = 0.0;
     return;
@@ -422,6 +423,15 @@ __device__ __forceinline__ void exp_fn(const TersoffParams& p, double x, double*
   const double xm1 = p.m == 3 ? x * x : 1.0;
   *e = exp(p.l3m * xm1 * x);
   *de = *e * p.m * p.l3m * xm1;
+}
+
+// zeta + (f_C g) e with f_C g rounded first, also where e = 1 (left to itself the
+// compiler would then fuse the product f_C g into the sum)
+template <bool L3>
+__device__ __forceinline__ double zeta_add(double fg, double e, double zeta) {
+  if (L3) return fma(fg, e, zeta);
+  asm("" : "+v"(fg));
+  return zeta + fg;
 }
 
 // List slot of the s-th kept pair of a bond mask (bit f: list slot f is kept).
@@ -438,9 +448,14 @@ __device__ __forceinline__ int kept_slot(unsigned long long m, int s) {
 // whose atoms all have at most LPA pairs skips the second slot of every lane.
 // One wavefront per work-group: an atom's lanes never span two (LPA <= 64), so
 // the barriers only order the wave's own LDS traffic, and waves of unequal
-// length (atoms with more pairs) do not wait for each other.
+// length (atoms with more pairs) do not wait for each other.  L3: lambda3 is
+// not 0 (without it the exponentials of a triplet and their derivatives go).
+// Bound: float64 instructions (216000 atoms), the chain of loads and
+// arithmetic of one pair (8000 atoms).  Measured, other pairs one after the
+// other with a test each and lists loaded after their counts: 216000 Si atoms
+// 33.5 -> 28.8 us, 8000 atoms 7.0 -> 6.2 us.
 constexpr int SITE_WG = 64;
-template <int LPA, int SPL>
+template <int LPA, int SPL, bool L3>
 __global__ void __launch_bounds__(SITE_WG) k_tersoff_site(TersoffArgs a, TersoffParams p) {
   __shared__ double sh[8][SITE_WG * SPL];
   const int tid = threadIdx.x;
@@ -448,18 +463,22 @@ __global__ void __launch_bounds__(SITE_WG) k_tersoff_site(TersoffArgs a, Tersoff
   const int gb = (tid - s0) * SPL;   // this atom's slot 0 in LDS
   const int64_t N = a.N;
   const int64_t i = ((int64_t)blockIdx.x * SITE_WG + tid) / LPA;
-  int n = 0;
-  if (a.bond_clear && blockIdx.x == 0 && tid == 0) *a.bond_clear = 0;
+  const int64_t ic = i < N ? i : N - 1;
+  // the count, the first list entry and the atom's position in flight together
+  // (and with the rebuild flag): an entry past the count, or of a list about
+  // to be rebuilt, is not used
+  int n = a.n_nb[ic];
+  int j0 = a.nbr[(int64_t)min(s0, a.max_nb - 1) * N + ic];
+  const double xi = a.pos[3 * ic], yi = a.pos[3 * ic + 1], zi = a.pos[3 * ic + 2];
   const bool build = a.bond_need && *a.bond_need;   // one value for the whole grid
-  if (!build) {
-    n = i < N ? a.n_nb[i] : 0;
-  } else {
+  asm volatile("" ::: "memory");                    // no load moves behind the branches below
+  if (a.bond_clear && blockIdx.x == 0 && tid == 0) *a.bond_clear = 0;
+  if (i >= N) n = 0;
+  if (build) {
     // bond lists out of the skin lists (BondBufs): the listed pairs closer
     // than rb in list order, LPA list slots at a time; their reverse slots
     // need every atom's mask and come from the gather kernel
     const int full = i < N ? a.full_n[i] : 0;
-    const int64_t ic = i < N ? i : 0;
-    const double xi = a.pos[3 * ic], yi = a.pos[3 * ic + 1], zi = a.pos[3 * ic + 2];
     unsigned long long m = 0;
     for (int f0 = 0; __ballot(f0 < full) != 0; f0 += LPA) {
       bool keep = false;
@@ -489,7 +508,11 @@ __global__ void __launch_bounds__(SITE_WG) k_tersoff_site(TersoffArgs a, Tersoff
 #pragma unroll
     for (int k = 0; k < SPL; ++k) {
       const int s = s0 + k * LPA;
-      if (s < n) a.bond_nbr[(int64_t)s * N + i] = a.full_nbr[(int64_t)kept_slot(m, s) * N + i];
+      if (s < n) {
+        const int j = a.full_nbr[(int64_t)kept_slot(m, s) * N + i];
+        a.bond_nbr[(int64_t)s * N + i] = j;
+        if (k == 0) j0 = j;
+      }
     }
   }
   double x[SPL], y[SPL], z[SPL], r[SPL], ir[SPL], fc[SPL], dfc[SPL], er[SPL], ea[SPL];
@@ -500,10 +523,10 @@ __global__ void __launch_bounds__(SITE_WG) k_tersoff_site(TersoffArgs a, Tersoff
     r[k] = ir[k] = 1.0;
     fc[k] = dfc[k] = er[k] = ea[k] = 0.0;
     if (s < n) {
-      const int64_t j = a.nbr[(int64_t)s * N + i];
-      x[k] = min_image(a.pos[3 * j] - a.pos[3 * i], a.box[0], a.ibox[0]);
-      y[k] = min_image(a.pos[3 * j + 1] - a.pos[3 * i + 1], a.box[1], a.ibox[1]);
-      z[k] = min_image(a.pos[3 * j + 2] - a.pos[3 * i + 2], a.box[2], a.ibox[2]);
+      const int64_t j = k == 0 ? j0 : a.nbr[(int64_t)s * N + i];
+      x[k] = min_image(a.pos[3 * j] - xi, a.box[0], a.ibox[0]);
+      y[k] = min_image(a.pos[3 * j + 1] - yi, a.box[1], a.ibox[1]);
+      z[k] = min_image(a.pos[3 * j + 2] - zi, a.box[2], a.ibox[2]);
       r[k] = sqrt(x[k] * x[k] + y[k] * y[k] + z[k] * z[k]);
       ir[k] = 1.0 / r[k];
       cutoff_fn(p, r[k], &fc[k], &dfc[k]);
@@ -524,6 +547,11 @@ __global__ void __launch_bounds__(SITE_WG) k_tersoff_site(TersoffArgs a, Tersoff
   // zeros to every sum below, so they are skipped, and such a pair's own
   // slot has nothing to compute (its energy, bracket weight and partials are
   // zero).
+  //
+  // The other pairs q != s of a bond go three at a time (a bond of an atom with
+  // four has three), o-th other = slot o + (o >= s): their LDS reads and angle
+  // terms are independent, only the sums chain.
+  constexpr int OTH = 3;
   double b[SPL], adb[SPL];
 #pragma unroll
   for (int k = 0; k < SPL; ++k) {
@@ -533,14 +561,20 @@ __global__ void __launch_bounds__(SITE_WG) k_tersoff_site(TersoffArgs a, Tersoff
     double u = 0.0;
     if (s < n && fc[k] != 0.0) {
       double zeta = 0.0;
-      for (int q = 0; q < n; ++q) {
-        if (q == s || sh[5][gb + q] == 0.0) continue;
-        const int l = gb + q;
-        const double cs = (x[k] * sh[0][l] + y[k] * sh[1][l] + z[k] * sh[2][l]) * (ir[k] * sh[4][l]);
-        const double g = angle_g(p, cs);
-        double e, de;
-        exp_fn(p, r[k] - sh[3][l], &e, &de);
-        zeta = fma(sh[5][l] * g, e, zeta);
+      for (int o0 = 0; o0 < n - 1; o0 += OTH) {
+        double term[OTH], e[OTH], fq[OTH];
+#pragma unroll
+        for (int v = 0; v < OTH; ++v) {
+          const int l = gb + min(o0 + v + (o0 + v >= s ? 1 : 0), n - 1);
+          fq[v] = o0 + v < n - 1 ? sh[5][l] : 0.0;
+          const double cs = (x[k] * sh[0][l] + y[k] * sh[1][l] + z[k] * sh[2][l]) * (ir[k] * sh[4][l]);
+          double de;
+          term[v] = angle_g(p, cs);
+          exp_fn<L3>(p, r[k] - sh[3][l], &e[v], &de);
+        }
+#pragma unroll
+        for (int v = 0; v < OTH; ++v)
+          if (fq[v] != 0.0) zeta = zeta_add<L3>(fq[v] * term[v], e[v], zeta);
       }
       // (beta zeta)^n and (1 + bz)^(-1/(2n)) through exp and log (bz = 0 where beta zeta = 0)
       const double bzeta = p.beta * zeta;
@@ -573,37 +607,42 @@ __global__ void __launch_bounds__(SITE_WG) k_tersoff_site(TersoffArgs a, Tersoff
     }
     // dU_i/dr_ij for this slot's pair j
     const double ux = x[k] * ir[k], uy = y[k] * ir[k], uz = z[k] * ir[k];
-    const double radial = 0.5 * (dfc[k] * (er[k] - b[k] * ea[k]) + fc[k] * (-p.l1 * er[k] + p.l2 * b[k] * ea[k]));
+    // (one association of the sum, so that its value does not depend on the build)
+    const double radial = 0.5 * fma(dfc[k], er[k] - b[k] * ea[k], fc[k] * (-p.l1 * er[k] + p.l2 * b[k] * ea[k]));
     const double ir2 = ir[k] * ir[k];
     double zx = 0.0, zy = 0.0, zz = 0.0;   // d zeta_ij / d r_ij
     double kx = 0.0, ky = 0.0, kz = 0.0;   // sum_{k != j} a_ik db_ik d zeta_ik / d r_ij
-    for (int q = 0; q < n; ++q) {
-      if (q == s || sh[5][gb + q] == 0.0) continue;
-      const int l = gb + q;
-      const double qx = sh[0][l], qy = sh[1][l], qz = sh[2][l], rq = sh[3][l];
-      const double iri = ir[k] * sh[4][l];   // 1 / (r_ij r_ik)
-      const double cs = (x[k] * qx + y[k] * qy + z[k] * qz) * iri;
-      // d cos theta / d r_ij = r_ik / (r_ij r_ik) - cos theta r_ij / r_ij^2
-      const double cr = cs * ir2;
-      const double cx = fma(qx, iri, -x[k] * cr);
-      const double cy = fma(qy, iri, -y[k] * cr);
-      const double cz = fma(qz, iri, -z[k] * cr);
-      double g, dg, e1, de1, e2, de2;
-      angle_fn(p, cs, &g, &dg);
-      exp_fn(p, r[k] - rq, &e1, &de1);
-      exp_fn(p, rq - r[k], &e2, &de2);
-      // zeta_ij's term: f_C(r_ik) (g' e1 dcos/dr_ij + g e1' u_ij)
-      const double fcq = sh[5][l];
-      const double za = fcq * dg * e1, zb = fcq * g * de1;
-      zx = fma(za, cx, fma(zb, ux, zx));
-      zy = fma(za, cy, fma(zb, uy, zy));
-      zz = fma(za, cz, fma(zb, uz, zz));
-      // zeta_ik's term through f_C(r_ij), g and e2 = exp(l3^m (r_ik - r_ij)^m), weighted by a_ik db_ik
-      const double w = sh[6][l];
-      const double ka = w * fc[k] * dg * e2, kb = w * g * (dfc[k] * e2 - fc[k] * de2);
-      kx = fma(ka, cx, fma(kb, ux, kx));
-      ky = fma(ka, cy, fma(kb, uy, ky));
-      kz = fma(ka, cz, fma(kb, uz, kz));
+    for (int o0 = 0; o0 < n - 1; o0 += OTH) {
+#pragma unroll
+      for (int v = 0; v < OTH; ++v) {
+        const int l = gb + min(o0 + v + (o0 + v >= s ? 1 : 0), n - 1);
+        const double fcq = o0 + v < n - 1 ? sh[5][l] : 0.0;
+        const double qx = sh[0][l], qy = sh[1][l], qz = sh[2][l], rq = sh[3][l];
+        const double iri = ir[k] * sh[4][l];   // 1 / (r_ij r_ik)
+        const double cs = (x[k] * qx + y[k] * qy + z[k] * qz) * iri;
+        // d cos theta / d r_ij = r_ik / (r_ij r_ik) - cos theta r_ij / r_ij^2
+        const double cr = cs * ir2;
+        const double cx = fma(qx, iri, -x[k] * cr);
+        const double cy = fma(qy, iri, -y[k] * cr);
+        const double cz = fma(qz, iri, -z[k] * cr);
+        double g, dg, e1, de1, e2, de2;
+        angle_fn(p, cs, &g, &dg);
+        exp_fn<L3>(p, r[k] - rq, &e1, &de1);
+        exp_fn<L3>(p, rq - r[k], &e2, &de2);
+        // zeta_ij's term: f_C(r_ik) (g' e1 dcos/dr_ij + g e1' u_ij)
+        const double za = fcq * dg * e1, zb = fcq * g * de1;
+        // zeta_ik's term through f_C(r_ij), g and e2 = exp(l3^m (r_ik - r_ij)^m), weighted by a_ik db_ik
+        const double w = sh[6][l];
+        const double ka = w * fc[k] * dg * e2, kb = w * g * (dfc[k] * e2 - fc[k] * de2);
+        if (fcq != 0.0) {
+          zx = fma(za, cx, L3 ? fma(zb, ux, zx) : zx);   // zb = 0 without lambda3
+          zy = fma(za, cy, L3 ? fma(zb, uy, zy) : zy);
+          zz = fma(za, cz, L3 ? fma(zb, uz, zz) : zz);
+          kx = fma(ka, cx, fma(kb, ux, kx));
+          ky = fma(ka, cy, fma(kb, uy, ky));
+          kz = fma(ka, cz, fma(kb, uz, kz));
+        }
+      }
     }
     dd[0] = radial * ux - 0.5 * (adb[k] * zx + kx);
     dd[1] = radial * uy - 0.5 * (adb[k] * zy + ky);
@@ -633,6 +672,10 @@ __device__ __forceinline__ void wave_lds_fence() {
 // too, a component per lane: 216000 atoms 22 us instead of 16 + 7.3 us in a
 // kernel of its own, and one launch fewer (a step of 8000 atoms 20.4 -> 15.3 us
 // with the bond build in the site kernel instead of one that mostly exits).
+// A step's two kernels are chains of dependent loads, so every load that needs
+// no other goes first, and the partials of bond lists with the positions: an
+// MD step of 216000 atoms 59.8 -> 54.9 us, of 512000 117 -> 108 us, of 8000
+// under the thermostat 17.4 -> 17.0 us.
 constexpr int GATHER_WG = 256;
 template <int LPA, int SPL>
 __global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, GatherArgs o) {
@@ -647,12 +690,25 @@ __global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, Gat
   double* tt = tot[wave];
   const int64_t N = a.N;
   const int64_t i0 = (int64_t)blockIdx.x * APB + (int64_t)wave * APW, i = i0 + g;
-  const bool built = a.bond_need && *a.bond_need;   // bond lists just built by the site kernel
-  const int n = i < N ? a.n_nb[i] : 0;
-  // the first round's list entry and reverse slot are loaded with the count,
-  // not after it (the rows below max_nb exist; entries at or past n are not used)
-  const bool row = i < N && s0 < a.max_nb;
-  int jl = row ? a.nbr[(int64_t)s0 * N + i] : 0, rl = row ? a.rev[(int64_t)s0 * N + i] : 0;
+  // Every load that needs no other goes first, without a branch (what a call
+  // does not use is read from an array that is there): the count, the first
+  // round's list entry and reverse slot (the rows below max_nb exist; entries
+  // at or past n are not used) and what component s0 needs at the end.
+  const int64_t ic = i < N ? i : N - 1;
+  const int64_t e0 = (int64_t)min(s0, a.max_nb - 1) * N + ic, qc = 3 * ic + min(s0, 2);
+  const bool ext = o.Fext || o.add_ext, comp = i < N && s0 < 3;
+  const int n_i = a.n_nb[ic];
+  int jl = a.nbr[e0], rl = a.rev[e0];
+  const int need = *(a.bond_need ? a.bond_need : a.n_nb);
+  const double x_q = a.pos[qc], e_i = (ext ? a.U : a.pos)[ic];
+  const double m_i = (o.vel || o.kick_vel ? o.mass : a.pos)[ic];
+  const double* pv = o.vel ? o.vel : a.pos;
+  const double va[3] = {pv[3 * ic], pv[3 * ic + 1], pv[3 * ic + 2]};
+  const double v_q = (o.kick_vel ? o.kick_vel : a.pos)[qc], ref_q = (o.drift_ref ? o.drift_ref : a.pos)[qc];
+  const double scale = (o.kick_scale ? o.kick_scale : a.pos)[2];
+  asm volatile("" ::: "memory");   // the loads stay up here
+  const int n = i < N ? n_i : 0;
+  const bool built = a.bond_need && need;   // bond lists just built by the site kernel
   // the reverse slots of new bond lists: bond s of i sits at the s-th kept
   // slot f of i's skin list, which is slot t = full_rev[f][i] in the list of
   // j; its bond slot in j's list is the number of j's kept slots below t
@@ -661,9 +717,9 @@ __global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, Gat
     const int t = a.full_rev[(int64_t)kept_slot(mi, s) * N + i];
     const unsigned long long mj = t >= 0 ? a.bond_mask[j] : 0ull;
     const int r = t >= 0 && ((mj >> t) & 1ull) ? __builtin_popcountll(mj & ((1ull << t) - 1ull)) : -1;
-    a.bond_rev[(int64_t)s * N + i] = r;
+    a.bond_rev[(int64_t)s * N + i] = r < 0 ? 0 : r;   // the call fails at its end; no read out of range until then
     if (r < 0) a.bond_flags[2] = 1;
-    return r < 0 ? 0 : r;   // the call fails at its end; no read out of range until then
+    return r < 0 ? 0 : r;
   };
   double sum[QL];
 #pragma unroll
@@ -680,14 +736,26 @@ __global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, Gat
       if (k > 0) jl = a.nbr[es], rl = a.rev[es];
       const int64_t j = jl;
       if (__builtin_expect(built, 0)) rl = reverse_slot(s, j);
-      const double r[3] = {min_image(a.pos[3 * j] - a.pos[3 * i], a.box[0], a.ibox[0]),
-                           min_image(a.pos[3 * j + 1] - a.pos[3 * i + 1], a.box[1], a.ibox[1]),
-                           min_image(a.pos[3 * j + 2] - a.pos[3 * i + 2], a.box[2], a.ibox[2])};
+      double dij[3], dji[3];
+      auto partials = [&]() {
+        const double* p = a.dd + 3 * es;
+        const double* q = a.dd + 3 * ((int64_t)rl * N + j);
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu) dij[mu] = p[mu], dji[mu] = q[mu];
+      };
+      // bond lists: nearly every pair is near, its partials are loaded with the
+      // positions
+      if (a.bond_need) partials();
+      const double pj[3] = {a.pos[3 * j], a.pos[3 * j + 1], a.pos[3 * j + 2]};
+      const double pi[3] = {a.pos[3 * i], a.pos[3 * i + 1], a.pos[3 * i + 2]};
+      asm volatile("" ::: "memory");
+      const double r[3] = {min_image(pj[0] - pi[0], a.box[0], a.ibox[0]),
+                           min_image(pj[1] - pi[1], a.box[1], a.ibox[1]),
+                           min_image(pj[2] - pi[2], a.box[2], a.ibox[2])};
       // a pair beyond R + D has zero partials both ways (written so by the site
       // kernel): nothing to load or add
       if (r[0] * r[0] + r[1] * r[1] + r[2] * r[2] < o.rcut2) {
-        const double* dij = a.dd + 3 * es;
-        const double* dji = a.dd + 3 * ((int64_t)rl * N + j);
+        if (!a.bond_need) partials();
 #pragma unroll
         for (int mu = 0; mu < 3; ++mu) {
           c[mu] = dij[mu] - dji[mu];
@@ -713,41 +781,36 @@ __global__ void __launch_bounds__(GATHER_WG) k_tersoff_gather(TersoffArgs a, Gat
   }
   wave_lds_fence();
   double mv2 = 0.0, d2 = 0.0;
-  if (i < N && s0 < 3) {   // component s0 of atom i
+  if (comp) {   // component s0 of atom i
     const double* t = tt + g * 12;
     double f = t[s0];
-    if (o.Fext || o.add_ext) {
-      double e = a.U[i];
-      if (o.vel) {
-        const double vx = o.vel[3 * i], vy = o.vel[3 * i + 1], vz = o.vel[3 * i + 2];
-        e += 0.5 * o.mass[i] * (vx * vx + vy * vy + vz * vz) * o.ke_unit;
-      }
+    if (ext) {
+      double e = e_i;
+      if (o.vel) e += 0.5 * m_i * (va[0] * va[0] + va[1] * va[1] + va[2] * va[2]) * o.ke_unit;
       const double fx = e * o.fe[s0] + (o.fe[0] * t[3 + s0] + o.fe[1] * t[6 + s0] + o.fe[2] * t[9 + s0]);
       if (o.Fext) o.Fext[3 * i + s0] = fx;
       if (o.add_ext) f += fx;
     }
     if (o.F) o.F[3 * i + s0] = f;
     if (o.kick_vel) {
-      // The rest of the step.  E_i's loads of v (the wave's own atoms) are back
-      // before any f is known, so before any component is written.
-      const double m = o.mass[i];
-      double v = o.kick_vel[3 * i + s0];
+      // The rest of the step (the loads of v above, E_i's too, precede every store)
+      double v = v_q;
       if (o.kick2) {   // end of a step: v += c F / m, under a thermostat v *= exp(-xi dt / 2)
-        v = v + o.kick_c * f / m;
-        if (o.kick_scale) v = v * o.kick_scale[2];
+        v = v + o.kick_c * f / m_i;
+        if (o.kick_scale) v = v * scale;
         if (o.kick_v32) o.kick_v32[3 * i + s0] = (float)v;
-        mv2 = m * v * v;
+        mv2 = m_i * v * v;
       }
       if (o.drift_pos) {   // start of the next: as k_md_step, into the other positions
-        v = v + o.kick_c * f / m;
+        v = v + o.kick_c * f / m_i;
         const double L = a.box[s0];
-        double x = a.pos[3 * i + s0] + o.drift_dt * v;
+        double x = x_q + o.drift_dt * v;
         x -= floor(x / L) * L;
         if (x >= L) x -= L;
         if (x < 0.0) x += L;
         o.drift_pos[3 * i + s0] = x;
         if (o.drift_ref) {
-          double d = x - o.drift_ref[3 * i + s0];
+          double d = x - ref_q;
           d -= L * rint(d / L);
           d2 = d * d;
         }
@@ -825,7 +888,10 @@ static hipError_t launch_pair_kernels(hipStream_t s, const TersoffArgs& a, const
   // 5..8 pairs: 4 lanes x 2 slots (most atoms of a crystal have 4 bonds, so
   // most waves run one slot round)
   constexpr int SL = LPA == 8 ? 4 : LPA, SPL = LPA / SL;
-  hipLaunchKernelGGL((k_tersoff_site<SL, SPL>), dim3(blocks_of(a.N * SL, SITE_WG)), dim3(SITE_WG), 0, s, a, p);
+  const dim3 grid(blocks_of(a.N * SL, SITE_WG));
+  if (p.l3m == 0.0) hipLaunchKernelGGL((k_tersoff_site<SL, SPL, false>), grid, dim3(SITE_WG), 0, s, a, p);
+  else
+    hipLaunchKernelGGL((k_tersoff_site<SL, SPL, true>), grid, dim3(SITE_WG), 0, s, a, p);
   if (e1) {
     hipError_t e = hipEventRecord(e1, s);
     if (e != hipSuccess) return e;
@@ -990,8 +1056,13 @@ __global__ void __launch_bounds__(3 * MD_ATOMS) k_md_nvt_start(double* __restric
   const int t = threadIdx.x;
   const int64_t q = (int64_t)blockIdx.x * (3 * MD_ATOMS) + t;
   const bool act = q < 3 * N;
-  double v = act ? vel[q] : 0.0, x = act ? pos[q] : 0.0;
-  const double f = act ? F[q] : 0.0, m = act ? mass[q / 3] : 1.0;
+  // every load first: the kernel is one chain of latencies
+  const int64_t qc = act ? q : 0;
+  double v = vel[qc], x = pos[qc], f = F[qc], m = mass[qc / 3], rq = 0.0;
+  if (ref) rq = ref[qc];
+  const double* state = n_part > 0 ? from : to;
+  const double st0 = state[0], st1 = state[1], st2 = state[2], st3 = state[3];
+  asm volatile("" ::: "memory");
   double scale;
   if (n_part > 0) {
     if (t < 64) {   // one wave; k_thermostat's sum: its threads' values, then its tree
@@ -1008,7 +1079,7 @@ __global__ void __launch_bounds__(3 * MD_ATOMS) k_md_nvt_start(double* __restric
       if (t == 0) sh[0] = sum;
     }
     if (t == 0) {
-      double st[4] = {from[0], from[1], from[2], from[3]};
+      double st[4] = {st0, st1, st2, st3};
       thermostat_update(sh[0], st, th, mode);
       new_scale = st[2];
       if (blockIdx.x == 0)
@@ -1017,7 +1088,7 @@ __global__ void __launch_bounds__(3 * MD_ATOMS) k_md_nvt_start(double* __restric
     __syncthreads();
     scale = new_scale;
   } else {
-    scale = to[2];
+    scale = st2;
   }
   double d2 = 0.0;
   if (act) {
@@ -1032,7 +1103,7 @@ __global__ void __launch_bounds__(3 * MD_ATOMS) k_md_nvt_start(double* __restric
     pos[q] = x;
     vel[q] = v;
     if (ref) {
-      double d = x - ref[q];
+      double d = x - rq;
       d -= L * rint(d / L);
       d2 = d * d;
     }

@@ -1209,7 +1209,7 @@ mhc_status mhc_synchronize(mhc_ctx* ctx) {
 // [dir][b][mu], then the Eq. 10 total [3], then (split) the split totals [dir][mu].
 // Small read-outs are written by the finishing kernel straight into the
 // context's pinned buffer (host memory that the GPU writes over PCIe): one
-// kernel and one synchronization, no copy (a push and HNEMA read of a 512-atom
+// kernel and one synchronization, no copy (a push and HNEMA read of a 64-atom
 // system: 75 us with two kernels and two copies into pageable memory, 38 us
 // now).  Larger ones go through d_out: 64 KB at PCIe rate is about what a copy
 // costs to start.
