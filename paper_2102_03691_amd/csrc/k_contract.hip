@@ -74,6 +74,7 @@ __device__ __forceinline__ int acc_row(int j, int half) { return 8 * (j >> 2) + 
 // step.
 typedef __attribute__((address_space(1))) const f32x4 gf32x4;
 constexpr int GEMV_ROWS = 8;
+constexpr int GEMV_SMALL_K = 4096;   // largest K_pad of k_gemv_small: 64 KB of LDS
 
 __global__ void __launch_bounds__(256)
 k_gemv_f32(const f32x4* __restrict__ E, const float* __restrict__ B, int n_steps, int64_t M_pad,
@@ -152,6 +153,161 @@ k_gemv_f32(const f32x4* __restrict__ E, const float* __restrict__ B, int n_steps
       out[(2 * M_pad + slot) * ld + t] = x * acc[r][3];
     }
   }
+}
+
+// The per-step path of small systems: input prep and contraction in one
+// launch.  A work-group takes 32 slots of one step as k_gemv_f32 (same sums,
+// same order) and first builds that step's operand for itself in LDS, from v
+// and W in whole lines, while its first rows of E load; the work-groups from
+// gemv_wgs on sum the Eq. 10 partials of 32 atoms x 32 steps as k_input_prep.
+// Bound: latency (a push is a chain of short kernels), hence one kernel fewer:
+// a push of one step of 8 to 216 atoms 17.5 -> 12.5 us, 512 atoms 21.4 -> 17.7
+// us, 1000 atoms 26.8 -> 23.5 us, 1331 atoms 31.7 -> 30.0 us.
+__global__ void __launch_bounds__(256)
+k_gemv_small(const f32x4* __restrict__ E, const float* __restrict__ v, const float* __restrict__ W,
+             const float* __restrict__ sqrt_m, const float* __restrict__ inv_sqrt_m, int N, int n_steps, int64_t M_pad,
+             int K_pad, float* __restrict__ out, int layout_g, int64_t ld, int gemv_wgs, double* __restrict__ jt_part,
+             int n_chunks, int t_pad) {
+  constexpr int R = GEMV_ROWS;
+  const int tid = threadIdx.x, lane = tid & 63;
+  if ((int)blockIdx.x >= gemv_wgs) {
+    const int wg = (int)blockIdx.x - gemv_wgs, chunk = wg % n_chunks, t = wg / n_chunks * 32 + (tid >> 3), sub = tid & 7;
+    constexpr int Q = ATOMS_PER_PREP / 8;
+    float vr[Q][3], Wr[Q][9];
+    const int64_t tc = min(t, n_steps - 1);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int64_t i = min(chunk * ATOMS_PER_PREP + sub + 8 * q, N - 1);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) vr[q][c] = v[(tc * N + i) * 3 + c];
+#pragma unroll
+      for (int c = 0; c < 9; ++c) Wr[q][c] = W[(tc * N + i) * 9 + c];
+    }
+    asm volatile("" ::: "memory");
+    double j[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (t < n_steps && chunk * ATOMS_PER_PREP + sub + 8 * q < N)
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu)   // products of two floats: exact
+          j[mu] += (double)Wr[q][3 * mu] * (double)vr[q][0] + (double)Wr[q][3 * mu + 1] * (double)vr[q][1] +
+                   (double)Wr[q][3 * mu + 2] * (double)vr[q][2];
+#pragma unroll
+    for (int off = 1; off < 8; off <<= 1)
+#pragma unroll
+      for (int mu = 0; mu < 3; ++mu) j[mu] += __shfl_xor(j[mu], off);
+    if (sub == 0 && t < t_pad)
+#pragma unroll
+      for (int mu = 0; mu < 3; ++mu) jt_part[((int64_t)t * n_chunks + chunk) * 3 + mu] = j[mu];
+    return;
+  }
+  __shared__ float sB[4][GEMV_SMALL_K];
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t n_rg = M_pad / R;                       // a multiple of 4: one step per work-group
+  const int64_t unit = (int64_t)blockIdx.x * 4 + wave;
+  const int t = (int)(unit / n_rg);
+  const int64_t rg = unit - (int64_t)t * n_rg;
+  const int KC = K_pad >> 2;                            // 16-byte units per row
+  const gf32x4* Er = (const gf32x4*)E + rg * R * KC;
+  const int n_it = KC / 64;                             // even
+  f32x4 e[2][R];
+  auto load = [&](f32x4 (&x)[R], int it) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = __builtin_nontemporal_load(Er + r * KC + it * 64 + lane);
+  };
+  load(e[0], 0);
+  load(e[1], 1);
+  const float* vt = v + (int64_t)t * N * 3;
+  const float* Wt = W + (int64_t)t * N * 9;
+  for (int i0 = 0; i0 < N; i0 += 256) {
+    const int i = min(i0 + tid, N - 1);
+    float a[3], w[9];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) a[c] = vt[3 * i + c];
+#pragma unroll
+    for (int c = 0; c < 9; ++c) w[c] = Wt[9 * i + c];
+    const float sm = sqrt_m[i], ism = inv_sqrt_m[i];
+    if (i0 + tid < N) {
+#pragma unroll
+      for (int al = 0; al < 3; ++al) {
+        sB[0][3 * i + al] = sm * a[al];
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu) sB[1 + mu][3 * i + al] = w[3 * mu + al] * ism;
+      }
+    }
+  }
+  for (int k = 3 * N + tid; k < K_pad; k += 256)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sB[c][k] = 0.f;
+  __syncthreads();
+  float acc[R][4];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[r][c] = 0.f;
+  auto consume = [&](const f32x4 (&x)[R], int it) {
+    f32x4 bv[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) bv[c] = *reinterpret_cast<const f32x4*>(&sB[c][4 * (it * 64 + lane)]);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        float s = acc[r][c];
+        s = fmaf(x[r].x, bv[c].x, s);
+        s = fmaf(x[r].y, bv[c].y, s);
+        s = fmaf(x[r].z, bv[c].z, s);
+        s = fmaf(x[r].w, bv[c].w, s);
+        acc[r][c] = s;
+      }
+  };
+  for (int it = 0; it < n_it; it += 2) {   // the prefetch past the end re-reads the last rows
+    consume(e[0], it);
+    load(e[0], min(it + 2, n_it - 1));
+    consume(e[1], it + 1);
+    load(e[1], min(it + 3, n_it - 1));
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      float s = acc[r][c];
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+      acc[r][c] = s;
+    }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (lane != r) continue;
+    const int64_t slot = rg * R + r;
+    const float x = acc[r][0];
+#pragma unroll
+    for (int mu = 0; mu < 3; ++mu) {
+      if (!layout_g) out[((int64_t)t * M_pad + slot) * 3 + mu] = x * acc[r][1 + mu];
+      else out[(mu * M_pad + slot) * ld + t] = x * acc[r][1 + mu];
+    }
+  }
+}
+
+// At most one wave per SIMD: beyond that k_gemv_steps or more waves per SIMD
+// hide the prep's latency, and every work-group would build the operand again.
+// The operand of a step has to fit a work-group's LDS (64 KB).  Inside the rule
+// no size measured was slower (64 to 1331 atoms, 1 to 32 steps).
+bool gemv_small(int n_steps, int64_t M_pad, int64_t K_pad) {
+  return K_pad <= GEMV_SMALL_K && M_pad / GEMV_ROWS * n_steps <= 1024;
+}
+
+hipError_t launch_gemv_small(hipStream_t s, const float* E, const float* v, const float* W, const float* sqrt_m,
+                             const float* inv_sqrt_m, int64_t N, int n_steps, int64_t M_pad, int64_t K_pad, float* out,
+                             int layout_g, int64_t ld, double* jt_part, int n_chunks, int t_pad) {
+  if (n_steps <= 0) return hipSuccess;
+  if (M_pad % M_ALIGN != 0 || K_pad % K_ALIGN_GEMV != 0 || !gemv_small(n_steps, M_pad, K_pad) || 3 * N > K_pad)
+    return hipErrorInvalidValue;
+  const int gemv_wgs = (int)(M_pad / (4 * GEMV_ROWS) * n_steps), tot_wgs = n_chunks * ((n_steps + 31) / 32);
+  hipLaunchKernelGGL(k_gemv_small, dim3((unsigned)(gemv_wgs + tot_wgs)), dim3(256), 0, s,
+                     reinterpret_cast<const f32x4*>(E), v, W, sqrt_m, inv_sqrt_m, (int)N, n_steps, M_pad, (int)K_pad, out,
+                     layout_g, ld, gemv_wgs, jt_part, n_chunks, t_pad);
+  return hipGetLastError();
 }
 
 // Several steps of the per-step path at once.  Streaming E once per step is

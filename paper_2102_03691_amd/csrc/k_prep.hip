@@ -286,19 +286,30 @@ __device__ __forceinline__ void input_prep_body(const float* v, const float* W, 
   const bool dm = (dir == DIR_ALL);
   double j0 = 0.0, j1 = 0.0, j2 = 0.0;
   double dd[3][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};   // split partials [nu][mu] (dir >= 0)
+  // the loads of the thread's four atoms together, from clamped addresses
+  constexpr int Q = ATOMS_PER_PREP / 8;
+  float vr[Q][3], Wr[Q][9], smr[Q], ismr[Q];
+  const int64_t tc = min(t, t_count - 1);
 #pragma unroll
-  for (int q = 0; q < ATOMS_PER_PREP / 8; ++q) {
+  for (int q = 0; q < Q; ++q) {
+    const int64_t i = min(i0 + sub + 8 * q, N - 1);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) vr[q][c] = v[(tc * N + i) * 3 + c];
+#pragma unroll
+    for (int c = 0; c < 9; ++c) Wr[q][c] = W[(tc * N + i) * 9 + c];
+    smr[q] = sqrt_m[i];
+    ismr[q] = inv_sqrt_m[i];
+  }
+  asm volatile("" ::: "memory");   // no load moves behind the branches below
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
     const int a = sub + 8 * q;
     const int64_t i = i0 + a;
     float u[3] = {0.f, 0.f, 0.f}, w[3][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
     if (t < t_count && i < N) {
-      const float* vp = v + ((int64_t)t * N + i) * 3;
-      const float* Wp = W + ((int64_t)t * N + i) * 9;
-      const float vx = vp[0], vy = vp[1], vz = vp[2];
-      const float sm = sqrt_m[i], ism = inv_sqrt_m[i];
-      float Wl[9];
-#pragma unroll
-      for (int c = 0; c < 9; ++c) Wl[c] = Wp[c];
+      const float vx = vr[q][0], vy = vr[q][1], vz = vr[q][2];
+      const float sm = smr[q], ism = ismr[q];
+      const float (&Wl)[9] = Wr[q];
       u[0] = sm * vx; u[1] = sm * vy; u[2] = sm * vz;
 #pragma unroll
       for (int mu = 0; mu < 3; ++mu)
@@ -317,9 +328,9 @@ __device__ __forceinline__ void input_prep_body(const float* v, const float* W, 
           for (int mu = 0; mu < 3; ++mu) dd[nu][mu] += (double)Wl[3 * mu + nu] * vv[nu];
       } else if (dir >= 0) {
         const double vd = dir == 0 ? dvx : (dir == 1 ? dvy : dvz);
-        dd[0][0] += (double)Wl[dir] * vd;
-        dd[0][1] += (double)Wl[3 + dir] * vd;
-        dd[0][2] += (double)Wl[6 + dir] * vd;
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu)
+          dd[0][mu] += (double)(dir == 0 ? Wl[3 * mu] : (dir == 1 ? Wl[3 * mu + 1] : Wl[3 * mu + 2])) * vd;
       }
     }
 #pragma unroll

@@ -1030,11 +1030,18 @@ static mhc_status run_block(mhc_ctx* ctx, const float* v, const float* W, int t_
   }
   for (int d = 0; d < ctx->n_dir; ++d) {
     const int dir = ctx->n_dir > 1 ? d : -1;
-    if ((st = block_front(ctx, v, W, t_count, nullptr, dir))) return st;
+    const bool small = c.t_block == 1 && dir < 0 && gemv_small(t_count, ctx->M_pad, ctx->K_pad);
+    if (!small && (st = block_front(ctx, v, W, t_count, nullptr, dir))) return st;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed && (st = timing_begin(ctx, &e0, &e1))) return st;
     int n_parts = 0, n_sub = 1;
-    if (c.t_block == 1) {
+    if (small) {
+      HIP_TRY(launch_gemv_small(ctx->stream, reinterpret_cast<const float*>(ctx->dE), v, W, ctx->d_sqrtm, ctx->d_isqrtm,
+                                ctx->N, t_count, ctx->M_pad, ctx->K_pad, ctx->dJ, gk ? 1 : 0, ctx->t_pad, ctx->d_jt,
+                                ctx->n_atom_chunks, ctx->t_pad),
+              "per-step input prep and contraction");
+      n_parts = t_count;
+    } else if (c.t_block == 1) {
       HIP_TRY(launch_gemv_f32(ctx->stream, reinterpret_cast<const float*>(ctx->dE),
                               reinterpret_cast<const float*>(ctx->dB), t_count, ctx->M_pad, ctx->K_pad, ctx->dJ,
                               gk ? 1 : 0, ctx->t_pad),

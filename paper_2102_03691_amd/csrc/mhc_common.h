@@ -91,6 +91,13 @@ hipError_t launch_nonfinite(hipStream_t s, const float* p, int64_t n, int* flag)
 hipError_t launch_gemv_f32(hipStream_t s, const float* E, const float* B, int n_steps, int64_t M_pad,
                            int64_t K_pad, float* out, int layout_g, int64_t ld);
 
+// The same for few waves and a small operand (gemv_small), straight from the
+// inputs: no input prep, the Eq. 10 partials come from this launch.
+bool gemv_small(int n_steps, int64_t M_pad, int64_t K_pad);
+hipError_t launch_gemv_small(hipStream_t s, const float* E, const float* v, const float* W, const float* sqrt_m,
+                             const float* inv_sqrt_m, int64_t N, int n_steps, int64_t M_pad, int64_t K_pad, float* out,
+                             int layout_g, int64_t ld, double* jt_part, int n_chunks, int t_pad);
+
 // Geometry of one system's T-batched contraction (plain data, shared with
 // the grouped launch, which keeps an array of these in device memory).
 struct GemmGeom {

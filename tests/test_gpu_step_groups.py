@@ -53,3 +53,39 @@ def test_grouped_steps_equal_single_steps(dims, nb, steps, methods):
         assert np.array_equal(ja, jb)
     if methods & DIRECTIONAL:
         assert rel(da, db) <= 1e-12
+
+
+@pytest.mark.parametrize("dims", [(1, 1, 1), (17, 10, 1), (19, 9, 1), (13, 15, 7), (683, 2, 1)])
+@pytest.mark.parametrize("methods", [HNEMA, HNEMA | GKMA])
+def test_small_step_path_edges(dims, methods):
+    """Steps pushed one by one, where the contraction builds its operand itself
+    (operand lengths around its padding to 512 and around the longest it takes,
+    4096), against one push of the first step count past that path (more than
+    1024 waves of 8 rows): the same bits per step."""
+    from paper_2102_03691_amd import ModalHC
+    lat = synth.BlochLattice(dims)
+    m = synth.masses(lat.n_atoms, "natural", 4)
+    steps = 1024 * 8 // (-(-lat.n_modes // 256) * 256) + 1
+    announce(f"small steps {dims} steps={steps} methods={methods}")
+    v, W = synth.gen_steps(9, m, 0, steps)
+    out = []
+    for piece in (steps, 1):
+        h = ModalHC(0)
+        h.load_system(m, lat.frequencies)
+        h.set_bins_uniform(7, 0.0, lat.f_max)
+        h.configure(methods=methods, t_block=1, corr_len=4 if methods & GKMA else 0)
+        for r0 in range(0, lat.n_modes, 512):
+            h.load_eigvec_rows(r0, lat.eig_rows(r0, min(512, lat.n_modes - r0)))
+        h.finalize()
+        jb = []
+        for s0 in range(0, steps, piece):
+            h.push(v[s0:s0 + piece], W[s0:s0 + piece])
+            if methods & GKMA:
+                jb.append(h.read_block_currents(min(piece, steps - s0)))
+        out.append((h.read_hnema(), np.concatenate(jb) if jb else None))
+        h.close()
+    (a, ja), (b, jb) = out
+    assert a[2] == b[2] == steps
+    assert rel(a[0], b[0]) <= 1e-12 and rel(a[1], b[1]) <= 1e-12
+    if methods & GKMA:
+        assert np.array_equal(ja, jb)
