@@ -52,14 +52,23 @@ __global__ void __launch_bounds__(256) k_shc_ring(const float* __restrict__ W, c
 }
 
 // The system of work-group (or block) b of a grouped launch: the last
-// descriptor whose first index is <= b (n_sys is small; a linear scan).
+// descriptor whose first index is <= b.
 __device__ __forceinline__ int shc_system_of(const ShcBlockDesc* __restrict__ d, int n_sys, int64_t b, int which) {
-  int q = 0;
-  for (int k = 1; k < n_sys; ++k) {
-    const int64_t f = which == 0 ? d[k].ring_blk0 : (which == 1 ? d[k].gram_wg0 : d[k].acc_blk0);
-    if (f <= b) q = k;
+  // 64 candidates at a time, one per lane (whole waves call this): one load's
+  // latency for up to 64 systems.  A scan over the systems waited for a load
+  // each, 3 us per work-group of 32 systems.
+  const int lane = threadIdx.x & 63;
+  int lo = 0, len = n_sys;
+  while (len > 1) {
+    const int step = (len + 63) / 64;
+    const ShcBlockDesc& e = d[lo + min(lane * step, len - 1)];
+    const int64_t f = which == 0 ? e.ring_blk0 : (which == 1 ? e.gram_wg0 : e.acc_blk0);
+    const unsigned long long m = __ballot(lane * step < len && f <= b);
+    const int k = __builtin_popcountll(m) - 1;   // the first system starts at 0
+    lo += k * step;
+    len = min(step, len - k * step);
   }
-  return q;
+  return lo;
 }
 
 __global__ void __launch_bounds__(256) k_shc_ring_group(const ShcBlockDesc* __restrict__ d, int n_sys) {
@@ -275,10 +284,16 @@ k_shc_gram(const float* __restrict__ vt, const float* __restrict__ ring, int64_t
 }
 
 // Several systems' products in one launch: the remapped id picks the system
-// (systems in order, each its work-groups in the single-system order).
+// (systems in order, each its work-groups in the single-system order).  Ids
+// are dealt to the XCDs `grain` at a time, in turn.
+__device__ __forceinline__ int shc_xcd_deal(int b, int G, int grain) {
+  const int full = G / (8 * grain) * (8 * grain);   // the rest in order
+  return b < full ? (b / 8 / grain * 8 + b % 8) * grain + b / 8 % grain : b;
+}
+
 __global__ void __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
-k_shc_gram_group(const ShcBlockDesc* __restrict__ d, int n_sys) {
-  const int v = shc_xcd_remap(blockIdx.x, gridDim.x);
+k_shc_gram_group(const ShcBlockDesc* __restrict__ d, int n_sys, int grain) {
+  const int v = shc_xcd_deal(blockIdx.x, gridDim.x, grain);
   const int q = shc_system_of(d, n_sys, v, 1);
   const ShcBlockDesc& e = d[q];
   shc_gram_tile(e.vt, e.ring, e.ring_len, e.ld, e.N, e.Np, e.t_count, e.s0, e.dk, e.n_kcs, e.n_ttiles,
@@ -337,9 +352,9 @@ hipError_t launch_shc_products(hipStream_t s, const float* vt, const float* ring
   return hipGetLastError();
 }
 
-hipError_t launch_shc_gram_group(hipStream_t s, const ShcBlockDesc* d, int n_sys, int64_t n_wgs) {
+hipError_t launch_shc_gram_group(hipStream_t s, const ShcBlockDesc* d, int n_sys, int64_t n_wgs, int grain) {
   if (n_wgs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_shc_gram_group, dim3((unsigned)n_wgs), dim3(256), 0, s, d, n_sys);
+  hipLaunchKernelGGL(k_shc_gram_group, dim3((unsigned)n_wgs), dim3(256), 0, s, d, n_sys, grain);
   return hipGetLastError();
 }
 

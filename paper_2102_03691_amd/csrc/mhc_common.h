@@ -288,7 +288,8 @@ int64_t shc_accum_blocks(int n_lags);
 // The grouped launches over n_sys descriptors (device memory); n_blocks /
 // n_wgs: the launch's total (the sum over the systems).
 hipError_t launch_shc_ring_group(hipStream_t s, const ShcBlockDesc* d, int n_sys, int64_t n_blocks, int t_count);
-hipError_t launch_shc_gram_group(hipStream_t s, const ShcBlockDesc* d, int n_sys, int64_t n_wgs);
+// grain >= 1: consecutive work-groups that go to one XCD
+hipError_t launch_shc_gram_group(hipStream_t s, const ShcBlockDesc* d, int n_sys, int64_t n_wgs, int grain);
 hipError_t launch_shc_accum_group(hipStream_t s, const ShcBlockDesc* d, int n_sys, int64_t n_blocks);
 // Kd[tau][mu][nu] = (ksum + kcomp)[nu][tau][mu] / (S - tau) (zero where S <= tau) and
 // K[tau][mu] = sum over nu in order (either may be null).

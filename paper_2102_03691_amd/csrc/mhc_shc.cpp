@@ -577,6 +577,8 @@ mhc_status group_block(mhc_shc_group* g, const float* const* v, const float* con
     if (g->sys[q]->cost <= SHC_FUSE_COST) fused.push_back(q);
   const int n = (int)fused.size();
   if (n == 0) return MHC_OK;
+  // the long work-groups first, so that short ones fill the end of the launch
+  std::stable_sort(fused.begin(), fused.end(), [&](int p, int q) { return g->sys[p]->dk > g->sys[q]->dk; });
   const int slot = (int)(g->next++ % mhc_shc_group::SLOTS);
   if (g->ev_pending[slot]) GHIP_TRY(hipEventSynchronize(g->ev[slot]), "descriptor slot wait");
   ShcBlockDesc* h = g->h_desc + (int64_t)slot * n_all;
@@ -616,7 +618,15 @@ mhc_status group_block(mhc_shc_group* g, const float* const* v, const float* con
   GHIP_TRY(hipEventRecord(g->ev[slot], g->stream), "event record");
   g->ev_pending[slot] = true;
   GHIP_TRY(launch_shc_ring_group(g->stream, d, n, rb, t_count), "virial rings");
-  GHIP_TRY(launch_shc_gram_group(g->stream, d, n, wg), "virial-velocity products");
+  // Work-groups of one length: an eighth of them in a row to each XCD (64
+  // systems of 100 atoms 247 us, dealt out 270 us).  Else the tiles of one dof
+  // range, at least 24 work-groups, dealt to the XCDs in turn: the XCDs end
+  // together (32 systems of 216 to 1000 atoms 647 -> 629 us, 4 of 216 to 1000
+  // atoms 148 -> 105 us).
+  const int tiles = (int)(shc_gram_wgs(t_count, g->sys[fused[0]]->n_lags, 1) / 3);
+  const bool even = g->sys[fused.front()]->dk == g->sys[fused.back()]->dk && wg % 8 == 0;
+  GHIP_TRY(launch_shc_gram_group(g->stream, d, n, wg, even ? (int)(wg / 8) : (23 + tiles) / tiles * tiles),
+           "virial-velocity products");
   GHIP_TRY(launch_shc_accum_group(g->stream, d, n, ab), "partial sums");
   for (int q : fused) g->sys[q]->S += t_count;
   return MHC_OK;

@@ -73,3 +73,27 @@ def test_shc_reads_around_the_pinned_size(n_lags):
     s.push(v, W)
     assert np.array_equal(s.read()[0], K)
     s.close()
+
+
+@pytest.mark.parametrize("atoms", [[40], [70, 40, 130, 40, 33], [40] * 16, [30 + k % 7 for k in range(70)]])
+@pytest.mark.parametrize("steps", [64, 100])
+def test_shc_group_work_group_orders(atoms, steps):
+    """Systems of a group on any XCD and in any order of the launch (one, mixed
+    lengths, equal lengths, more systems than a wave has lanes) give the bits
+    of their own pushes."""
+    import torch
+    from paper_2102_03691_amd import ModalSHC, SHCGroup
+    announce(f"shc group n={len(atoms)} steps={steps}")
+    ins = [synth.gen_steps(k, synth.masses(N, "natural", k), 0, steps) for k, N in enumerate(atoms)]
+    stream = torch.cuda.Stream()
+    got = [ModalSHC(N, 70, 64, stream=stream.cuda_stream) for N in atoms]
+    group = SHCGroup(got)
+    group.push([v for v, _ in ins], [W for _, W in ins])
+    for N, (v, W), s in zip(atoms, ins, got):
+        one = ModalSHC(N, 70, 64)
+        one.push(v, W)
+        assert np.array_equal(one.read()[0], s.read()[0])
+        one.close()
+    group.close()
+    for s in got:
+        s.close()
