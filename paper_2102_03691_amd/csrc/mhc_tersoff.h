@@ -20,7 +20,7 @@ struct CellGrid {
 // and cpos [N][3] (the atoms by cell and their positions); count [n_cells]
 // (zero between searches), start [n_cells + 1]; tile_sums [ceil(n_cells / 1024)]
 // (scan workspace); most [ceil(N / 16)] (largest counts of the search's
-// work-groups); flags[0] = largest neighbour count found, flags[1] = 1 if a
+// work-groups); flags (host memory) [0] = largest neighbour count found, flags[1] = 1 if a
 // reverse slot was missing, flags[2] = largest count inside the bond lists'
 // cutoff.
 struct NeighborBufs {

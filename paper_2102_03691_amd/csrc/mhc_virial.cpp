@@ -42,7 +42,7 @@ struct mhc_virial {
   bool lists_ok = false;
 
   std::vector<void*> allocs;
-  void* h_read = nullptr;   // 64 bytes of pinned memory that flags and the thermostat are read back into
+  void* h_read = nullptr;   // 64 bytes of pinned memory: the search's flags (last 16), bond flags and thermostat read back
   double* d_mass = nullptr;
   NeighborBufs nb{};
   double *d_dd = nullptr, *d_U = nullptr;
@@ -249,7 +249,7 @@ mhc_status mhc_virial_create(int device, void* hip_stream, int64_t n_atoms, cons
   bool ok = valloc(v, N, &v->d_mass) && valloc(v, MN, &b.nbr) && valloc(v, MN, &b.rev) && valloc(v, N, &b.n_nb) &&
             valloc(v, N, &b.cell_of) && valloc(v, N, &b.place) && valloc(v, N, &b.atoms) &&
             valloc(v, 3 * N, &b.cpos) && valloc(v, n_cells, &b.count) && valloc(v, n_cells + 1, &b.start) &&
-            valloc(v, (n_cells + 1023) / 1024, &b.tile_sums) && valloc(v, (N + 15) / 16, &b.most) && valloc(v, 3, &b.flags) &&
+            valloc(v, (n_cells + 1023) / 1024, &b.tile_sums) && valloc(v, (N + 15) / 16, &b.most) &&
             valloc(v, 3 * MN, &v->d_dd) && valloc(v, N, &v->d_U) && valloc(v, 3 * N, &v->d_F) &&
             valloc(v, 8, &v->d_thermo) && valloc(v, 3 * N, &v->d_pos2) &&
             valloc(v, std::max(md_nvt_parts(N), gather_parts(N, 64)), &v->d_kepart) &&
@@ -261,6 +261,9 @@ mhc_status mhc_virial_create(int device, void* hip_stream, int64_t n_atoms, cons
     v->h_read = nullptr;
     return cleanup(MHC_ERR_OOM, "pinned allocation failed");
   }
+  // the search's kernels write their three results straight into the last 16
+  // bytes of the pinned buffer: no copy behind the search
+  b.flags = static_cast<int*>(v->h_read) + 12;
   v->bb.need = v->bb.flags + 8;
   v->bond_skin = std::min(rc - (p.R + p.D), 0.5);
   if (launch_zero_i32(v->stream, b.count, (int)n_cells) != hipSuccess ||
@@ -295,8 +298,7 @@ mhc_status mhc_virial_neighbors(mhc_virial* v, const double* pos, int32_t* max_f
   v->lists_ok = false;
   VHIP_TRY(launch_neighbors(v->stream, pos, v->N, v->cg, v->rc, v->tp.R + v->tp.D + v->bond_skin, v->max_nb, v->nb),
            "neighbour search");
-  const int* flags = static_cast<const int*>(v->h_read);
-  VHIP_TRY(hipMemcpyAsync(v->h_read, v->nb.flags, 3 * sizeof(int), hipMemcpyDeviceToHost, v->stream), "read flags");
+  const int* flags = v->nb.flags;
   VHIP_TRY(hipStreamSynchronize(v->stream), "neighbour search sync");
   if (max_found) *max_found = flags[0];
   if (flags[0] > v->max_nb)

@@ -40,3 +40,24 @@ def test_lists_at_the_edges(cells, drop, skin):
         for i, r in enumerate(ref):
             assert counts[i] == len(r) and np.array_equal(lists[i, : counts[i]], sorted(r)) and (lists[i, counts[i]:] == -1).all()
     v.close()
+
+
+@pytest.mark.parametrize("cells,keep", [((10, 10, 10), 1000), ((15, 15, 15), 2600), ((19, 19, 19), 5000),
+                                        ((20, 20, 20), 5900)])
+def test_scan_tiles(cells, keep):
+    """Few atoms in many cells: 6, 20, 39 and 46 tiles of the cell scan (its own
+    counts up to 40 tiles, 16 at a time; sums of tiles above)."""
+    import torch
+    import oracle.virial as ov
+    from paper_2102_03691_amd import ModalVirial, tersoff_si
+    announce(f"neighbour search {cells} keep={keep}")
+    pos, box = synth.diamond(cells, sigma=0.08, seed=7)
+    pos = pos[np.random.default_rng(8).permutation(len(pos))[:keep]]
+    ref = ov.neighbor_lists(pos, box, 3.0)
+    v = ModalVirial(synth.masses(len(pos)), box, tersoff_si(), max_neighbors=8, skin=0.0)
+    for _ in range(2):
+        assert v.neighbors(torch.as_tensor(pos, device="cuda:0")) == max(len(r) for r in ref)
+        counts, lists = v.read_neighbors()
+        for i, r in enumerate(ref):
+            assert counts[i] == len(r) and np.array_equal(lists[i][: len(r)], r)
+    v.close()
