@@ -74,7 +74,41 @@ __device__ __forceinline__ int acc_row(int j, int half) { return 8 * (j >> 2) + 
 // step.
 typedef __attribute__((address_space(1))) const f32x4 gf32x4;
 constexpr int GEMV_ROWS = 8;
+constexpr int64_t GEMV_SMALL_UNITS = 4096, GEMV_SMALL_DOFS = 4096 * 1536;   // waves, waves x K_pad
 constexpr int GEMV_SMALL_K = 4096;   // largest K_pad of k_gemv_small: 64 KB of LDS
+
+// The sums over the 64 lanes of 8 rows x 4 channels, and their products to out.
+// At each of the first three exchanges a lane keeps half of its rows and sends
+// the other half (a + b = b + a, so every sum has the butterfly's bits): 40
+// exchanges instead of 192.  Lane l ends with row l / 8 and stores J^mu for
+// mu = l % 8 < 3.
+__device__ __forceinline__ void gemv_store_rows(float (&acc)[GEMV_ROWS][4], int lane, int64_t row0, int t, int64_t M_pad,
+                                                float* __restrict__ out, int layout_g, int64_t ld) {
+  static_assert(GEMV_ROWS == 8, "three exchanges leave one row per lane");
+#pragma unroll
+  for (int off = 32, n = 4; n > 0; off >>= 1, n >>= 1) {
+    const bool up = (lane & off) != 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (r >= n) break;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const float keep = up ? acc[r + n][c] : acc[r][c], send = up ? acc[r][c] : acc[r + n][c];
+        acc[r][c] = keep + __shfl_xor(send, off);
+      }
+    }
+  }
+#pragma unroll
+  for (int off = 4; off > 0; off >>= 1)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[0][c] += __shfl_xor(acc[0][c], off);
+  const int mu = lane & 7;
+  if (mu >= 3) return;
+  const int64_t slot = row0 + (lane >> 3);
+  const float j = acc[0][0] * (mu == 0 ? acc[0][1] : (mu == 1 ? acc[0][2] : acc[0][3]));
+  if (!layout_g) out[((int64_t)t * M_pad + slot) * 3 + mu] = j;
+  else out[(mu * M_pad + slot) * ld + t] = j;
+}
 
 __global__ void __launch_bounds__(256)
 k_gemv_f32(const f32x4* __restrict__ E, const float* __restrict__ B, int n_steps, int64_t M_pad,
@@ -130,29 +164,7 @@ k_gemv_f32(const f32x4* __restrict__ E, const float* __restrict__ B, int n_steps
     consume(eb, bb);
     __builtin_amdgcn_sched_barrier(0);
   }
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float a = acc[r][c];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-      acc[r][c] = a;
-    }
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    if (lane != r) continue;
-    const int64_t slot = rg * R + r;
-    const float x = acc[r][0];
-    if (!layout_g) {
-      float* o = out + ((int64_t)t * M_pad + slot) * 3;
-      o[0] = x * acc[r][1]; o[1] = x * acc[r][2]; o[2] = x * acc[r][3];
-    } else {
-      out[(0 * M_pad + slot) * ld + t] = x * acc[r][1];
-      out[(1 * M_pad + slot) * ld + t] = x * acc[r][2];
-      out[(2 * M_pad + slot) * ld + t] = x * acc[r][3];
-    }
-  }
+  gemv_store_rows(acc, lane, rg * R, t, M_pad, out, layout_g, ld);
 }
 
 // The per-step path of small systems: input prep and contraction in one
@@ -161,8 +173,9 @@ k_gemv_f32(const f32x4* __restrict__ E, const float* __restrict__ B, int n_steps
 // and W in whole lines, while its first rows of E load; the work-groups from
 // gemv_wgs on sum the Eq. 10 partials of 32 atoms x 32 steps as k_input_prep.
 // Bound: latency (a push is a chain of short kernels), hence one kernel fewer:
-// a push of one step of 8 to 216 atoms 17.5 -> 12.5 us, 512 atoms 21.4 -> 17.7
-// us, 1000 atoms 26.8 -> 23.5 us, 1331 atoms 31.7 -> 30.0 us.
+// a push of one step of 8 to 216 atoms 17.5 -> 8.5 us, 512 atoms 21.4 -> 12
+// us, 1000 atoms 26.8 -> 18 us, 1331 atoms 31.7 -> 25 us (of which 2 us from
+// 40 exchanges instead of 192 at the end, and 2 us from the bin sums).
 __global__ void __launch_bounds__(256)
 k_gemv_small(const f32x4* __restrict__ E, const float* __restrict__ v, const float* __restrict__ W,
              const float* __restrict__ sqrt_m, const float* __restrict__ inv_sqrt_m, int N, int n_steps, int64_t M_pad,
@@ -261,40 +274,26 @@ k_gemv_small(const f32x4* __restrict__ E, const float* __restrict__ v, const flo
         acc[r][c] = s;
       }
   };
-  for (int it = 0; it < n_it; it += 2) {   // the prefetch past the end re-reads the last rows
+  for (int it = 0; it < n_it; it += 2) {
+    const bool more = it + 2 < n_it;
     consume(e[0], it);
-    load(e[0], min(it + 2, n_it - 1));
+    if (more) load(e[0], it + 2);
     consume(e[1], it + 1);
-    load(e[1], min(it + 3, n_it - 1));
+    if (more) load(e[1], it + 3);
   }
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float s = acc[r][c];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-      acc[r][c] = s;
-    }
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    if (lane != r) continue;
-    const int64_t slot = rg * R + r;
-    const float x = acc[r][0];
-#pragma unroll
-    for (int mu = 0; mu < 3; ++mu) {
-      if (!layout_g) out[((int64_t)t * M_pad + slot) * 3 + mu] = x * acc[r][1 + mu];
-      else out[(mu * M_pad + slot) * ld + t] = x * acc[r][1 + mu];
-    }
-  }
+  gemv_store_rows(acc, lane, rg * R, t, M_pad, out, layout_g, ld);
 }
 
-// At most one wave per SIMD: beyond that k_gemv_steps or more waves per SIMD
-// hide the prep's latency, and every work-group would build the operand again.
-// The operand of a step has to fit a work-group's LDS (64 KB).  Inside the rule
-// no size measured was slower (64 to 1331 atoms, 1 to 32 steps).
+// The operand of a step has to fit a work-group's LDS (64 KB), and the waves
+// times the operand's length stay under 4096 x 1536: every work-group builds
+// the operand again and reads its rows of E for one step, which k_gemv_steps
+// reads for four.  Measured, small / k_gemv_f32 or k_gemv_steps: 64 atoms, 100
+// steps 20 / 28 us; 512 atoms, 16 steps 36 / 42; 729 atoms, 6 steps 27 / 36,
+// 8 steps 38 / 38, 11 steps 45 / 42; 1331 atoms, 3 steps 41 / 41, 4 steps 44 /
+// 42.
 bool gemv_small(int n_steps, int64_t M_pad, int64_t K_pad) {
-  return K_pad <= GEMV_SMALL_K && M_pad / GEMV_ROWS * n_steps <= 1024;
+  const int64_t units = M_pad / GEMV_ROWS * n_steps;
+  return K_pad <= GEMV_SMALL_K && units <= GEMV_SMALL_UNITS && units * K_pad <= GEMV_SMALL_DOFS;
 }
 
 hipError_t launch_gemv_small(hipStream_t s, const float* E, const float* v, const float* W, const float* sqrt_m,

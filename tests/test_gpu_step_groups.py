@@ -55,17 +55,18 @@ def test_grouped_steps_equal_single_steps(dims, nb, steps, methods):
         assert rel(da, db) <= 1e-12
 
 
-@pytest.mark.parametrize("dims", [(1, 1, 1), (17, 10, 1), (19, 9, 1), (13, 15, 7), (683, 2, 1)])
+@pytest.mark.parametrize("dims", [(1, 1, 1), (16, 10, 1), (23, 7, 1), (21, 64, 1), (269, 5, 1)])
 @pytest.mark.parametrize("methods", [HNEMA, HNEMA | GKMA])
 def test_small_step_path_edges(dims, methods):
     """Steps pushed one by one, where the contraction builds its operand itself
     (operand lengths around its padding to 512 and around the longest it takes,
     4096), against one push of the first step count past that path (more than
-    1024 waves of 8 rows): the same bits per step."""
+    4096 waves of 8 rows, or 4096 x 1536 waves x dofs): the same bits per step."""
     from paper_2102_03691_amd import ModalHC
     lat = synth.BlochLattice(dims)
     m = synth.masses(lat.n_atoms, "natural", 4)
-    steps = 1024 * 8 // (-(-lat.n_modes // 256) * 256) + 1
+    k_pad = -(-96 * -(-lat.n_atoms // 32) // 512) * 512
+    steps = min(4096, 4096 * 1536 // k_pad) * 8 // (-(-lat.n_modes // 256) * 256) + 1
     announce(f"small steps {dims} steps={steps} methods={methods}")
     v, W = synth.gen_steps(9, m, 0, steps)
     out = []
