@@ -506,7 +506,7 @@ mhc_status mhc_shc_kernel_timing(mhc_shc* c, int64_t* launches, double* total_ms
 // would start staggered instead of together, and the ones that share ring
 // rows would no longer read them at the same time (measured: 16 systems of
 // 0.6k..8k atoms fused 2.97 ms per block against 2.13 ms one by one; 64
-// systems of 0.2k..1k atoms 1.91 against 2.56 ms).  Each system's arithmetic
+// systems of 0.2k..1k atoms 1.38 against 2.56 ms).  Each system's arithmetic
 // and summation order are those of its own push, so the results are the
 // same bits.  The descriptors of a block go through a ring of pinned
 // host slots and device slots; a host slot is refilled only after the event
