@@ -127,14 +127,19 @@ typedef struct {
 
 /* Work split of the T-batched contraction (results agree to rounding; each
  * choice is deterministic for a given device):
- *   AUTO     SPLIT where it shortens the launch by 5 % or more, else TILES
+ *   AUTO     SPLIT where it shortens the launch by 5 % or more, else TILES;
+ *            where their tiles are too few to fill the GPU, the same sums
+ *            (the same bits) with one channel per wave and 32-step tiles
+ *            (mhc_last_kernel tells)
  *   TILES    one output tile per work-group
  *   STREAMK  equal contiguous ranges of (tile, k-stage) iterations per CU,
  *            split tiles summed in a fixed order by a second kernel
  *   SPLIT    one work-group per CU: whole tiles round by round, then the
  *            tiles of the last, partial round cut along k so that every CU
  *            takes part; the pieces of a tile are summed in a fixed order
- *            by whichever work-group finishes its piece last              */
+ *            by whichever work-group finishes its piece last
+ * The direction split as one contraction has tiles only: AUTO as above, any
+ * other value one tile after another per work-group.                      */
 enum { MHC_SCHED_AUTO = 0, MHC_SCHED_TILES = 1, MHC_SCHED_STREAMK = 2, MHC_SCHED_SPLIT = 3 };
 
 /* ---------------------------------------------------------------- lifetime */
@@ -327,7 +332,10 @@ mhc_status mhc_load_state(mhc_ctx *ctx, const void *buf, size_t len);
 /* ------------------------------------------------------------ diagnostics */
 
 /* Enable (1) or disable (0, the default) HIP-event timing of the dominant
- * contraction kernel (one event pair per launch on the context stream).
+ * contraction (one event pair per launch on the context stream; with AUTO the
+ * pair encloses whatever computes the contraction: small per-step systems'
+ * kernel also prepares its inputs and sums Eq. 10, and whole tiles followed by
+ * a rest one channel per wave are two kernels and a fill).
  * Errors: INVALID_ARG. */
 mhc_status mhc_set_timing(mhc_ctx *ctx, int enable);
 
@@ -339,10 +347,15 @@ mhc_status mhc_kernel_timing(mhc_ctx *ctx, int64_t *launches, double *total_ms);
 /* Bytes of device memory held by the context (basis, buffers, accumulators). */
 mhc_status mhc_device_bytes(mhc_ctx *ctx, int64_t *bytes);
 
-/* Work split the last T-batched contraction of this context actually used
- * (MHC_SCHED_TILES, _STREAMK or _SPLIT; what AUTO resolved to), or 0 when no
- * batched block has run yet (also for t_block = 1).  Errors: INVALID_ARG. */
+/* Work split whose sums the last T-batched contraction of this context
+ * computed (MHC_SCHED_TILES, _STREAMK or _SPLIT; what AUTO resolved to), or
+ * 0 when no batched block has run yet (also for t_block = 1).
+ * Errors: INVALID_ARG. */
 mhc_status mhc_last_schedule(mhc_ctx *ctx, int32_t *schedule);
+
+/* Name of the contraction kernel of the last block pushed to this context on
+ * its own (static string; "" before any push, and with ctx == NULL). */
+const char *mhc_last_kernel(const mhc_ctx *ctx);
 
 /* ------------------------------------------------------- grouped systems
  * Many independent systems (uneven sizes, HNEMA and GKMA mixed) advanced

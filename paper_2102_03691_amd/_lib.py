@@ -92,6 +92,7 @@ def library():
         "mhc_kernel_timing": (i32, [vp, P(i64), P(dbl)]),
         "mhc_device_bytes": (i32, [vp, P(i64)]),
         "mhc_last_schedule": (i32, [vp, P(i32)]),
+        "mhc_last_kernel": (C.c_char_p, [vp]),
         "mhc_shc_create": (i32, [C.c_int, vp, i64, i32, i32, P(vp)]),
         "mhc_shc_destroy": (i32, [vp]),
         "mhc_shc_last_error": (C.c_char_p, [vp]),
@@ -383,6 +384,10 @@ class ModalHC:
         s = C.c_int32()
         self._check(self._lib.mhc_last_schedule(self._h, C.byref(s)), "last_schedule")
         return s.value
+
+    def last_kernel(self):
+        """Name of the contraction kernel of the last block pushed on its own ("" before any)."""
+        return self._lib.mhc_last_kernel(self._h).decode()
 
 
 class ModalGroup:

@@ -298,7 +298,8 @@ bool gemv_small(int n_steps, int64_t M_pad, int64_t K_pad) {
 
 hipError_t launch_gemv_small(hipStream_t s, const float* E, const float* v, const float* W, const float* sqrt_m,
                              const float* inv_sqrt_m, int64_t N, int n_steps, int64_t M_pad, int64_t K_pad, float* out,
-                             int layout_g, int64_t ld, double* jt_part, int n_chunks, int t_pad) {
+                             int layout_g, int64_t ld, double* jt_part, int n_chunks, int t_pad, const char** kernel) {
+  *kernel = "k_gemv_small";
   if (n_steps <= 0) return hipSuccess;
   if (M_pad % M_ALIGN != 0 || K_pad % K_ALIGN_GEMV != 0 || !gemv_small(n_steps, M_pad, K_pad) || 3 * N > K_pad)
     return hipErrorInvalidValue;
@@ -420,7 +421,8 @@ k_gemv_steps(const f32x4* __restrict__ E, const float* __restrict__ B, int n_ste
 }
 
 hipError_t launch_gemv_f32(hipStream_t s, const float* E, const float* B, int n_steps, int64_t M_pad,
-                           int64_t K_pad, float* out, int layout_g, int64_t ld) {
+                           int64_t K_pad, float* out, int layout_g, int64_t ld, const char** kernel) {
+  *kernel = "k_gemv_f32";
   if (n_steps <= 0) return hipSuccess;
   if (M_pad % M_ALIGN != 0 || K_pad % K_ALIGN_GEMV != 0) return hipErrorInvalidValue;
   const int64_t units = (M_pad / GEMV_ROWS) * n_steps;
@@ -431,6 +433,7 @@ hipError_t launch_gemv_f32(hipStream_t s, const float* E, const float* B, int n_
   if (units > GEMV_STEPS_MIN_UNITS && n_steps >= 2) {
     const int64_t wgs = (M_pad / (4 * GEMV_ROWS)) * ((n_steps + GEMV_TS - 1) / GEMV_TS);
     if (wgs > INT32_MAX) return hipErrorInvalidValue;
+    *kernel = "k_gemv_steps";
     hipLaunchKernelGGL(k_gemv_steps, dim3((unsigned)wgs), dim3(256), 0, s, reinterpret_cast<const f32x4*>(E), B,
                        n_steps, M_pad, K_pad, out, layout_g, ld);
     return hipGetLastError();
@@ -1406,7 +1409,7 @@ static hipError_t launch_chan(hipStream_t s, const GemmGeom& g, const SplitPlan&
 template <int PREC, int WM, int WT, int MB, bool TR>
 static hipError_t launch_gemm_shape(hipStream_t s, const void* E, const void* B, float* out, float* ws,
                                     int64_t ws_floats, int* tile_cnt, GemmGeom g, int n_mtiles, int n_cu,
-                                    int sched, int* used, int* n_sub) {
+                                    int sched, int* used, int* n_sub, const char** kernel) {
   constexpr int NREG = MB * 4 * 16;
   const int64_t n_tiles = (int64_t)n_mtiles * g.n_ntiles;
   g.total_iters = n_tiles * g.n_stages;
@@ -1422,13 +1425,15 @@ static hipError_t launch_gemm_shape(hipStream_t s, const void* E, const void* B,
                                 sched == MHC_SCHED_AUTO ? 0.05 : 0.0, &sp, &stages);
   // Too few tiles to fill the chip (in the last round, if the split has whole
   // rounds before it): one channel per wave, with the split's pieces, whose
-  // sums are the same whoever adds them
+  // sums are the same whoever adds them.  A schedule that the caller names
+  // runs the kernel it names.
   const int64_t rest = split ? sp.R : n_tiles;
   const int64_t units = rest * WM * MB * WT;
-  if (sched != MHC_SCHED_STREAMK &&
+  if (sched == MHC_SCHED_AUTO &&
       chan_us(PREC, units, g.n_stages, n_cu) <
           tile_us(PREC, stages - (double)sp.q * g.n_stages, MB, split ? sp.m : 1)) {
     *used = split ? MHC_SCHED_SPLIT : MHC_SCHED_TILES;
+    *kernel = sp.q > 0 ? "k_gemm + k_gemm_chan" : "k_gemm_chan";
     *n_sub = TR ? WT : 1;
     if (sp.q > 0) {
       GemmGeom w = g;
@@ -1452,8 +1457,10 @@ static hipError_t launch_gemm_shape(hipStream_t s, const void* E, const void* B,
     sp.cnt = tile_cnt;
     hipLaunchKernelGGL((k_gemm_split<PREC, WM, WT, MB, TR>), dim3((unsigned)n_cu), dim3(256), 0, s, ws, g, sp);
     *used = MHC_SCHED_SPLIT;
+    *kernel = "k_gemm_split";
     return hipGetLastError();
   }
+  *kernel = "k_gemm";
   int64_t G = n_tiles;
   g.ipw = g.n_stages;
   // Stream-K only on request: work-groups that start at different k-stages no
@@ -1483,7 +1490,7 @@ template <int PREC>
 static hipError_t launch_gemm_prec(hipStream_t s, const void* E, const void* B, int64_t M_pad, int64_t K_pad, int ntb,
                                    float* out, int layout_g, int* n_parts, float* ws, int64_t ws_floats,
                                    int* tile_cnt, int n_cu, int sched, const float* row_scale,
-                                   const float* col_scale, int* used, int* n_sub) {
+                                   const float* col_scale, int* used, int* n_sub, const char** kernel) {
   GemmGeom g{};
   g.K_pad = K_pad;
   g.M_pad = M_pad;
@@ -1497,9 +1504,9 @@ static hipError_t launch_gemm_prec(hipStream_t s, const void* E, const void* B, 
   // slot-major one
 #define MHC_SHAPE(WM, WT, MB, ROWS)                                                                              \
   (layout_g ? launch_gemm_shape<PREC, WM, WT, MB, false>(s, E, B, out, ws, ws_floats, tile_cnt, g,               \
-                                                         (int)(M_pad / (ROWS)), n_cu, sched, used, n_sub)       \
+                                                         (int)(M_pad / (ROWS)), n_cu, sched, used, n_sub, kernel)       \
             : launch_gemm_shape<PREC, WM, WT, MB, true>(s, E, B, out, ws, ws_floats, tile_cnt, g,                \
-                                                        (int)(M_pad / (ROWS)), n_cu, sched, used, n_sub))
+                                                        (int)(M_pad / (ROWS)), n_cu, sched, used, n_sub, kernel))
   if (ntb % 4 == 0) {
     // 128 slots x 4 t-blocks per tile
     g.n_ntiles = ntb / 4;
@@ -1519,11 +1526,11 @@ static hipError_t launch_gemm_prec(hipStream_t s, const void* E, const void* B, 
 hipError_t launch_gemm(hipStream_t s, int prec, const void* E, const void* B, int64_t M_pad, int64_t K_pad,
                        int ntb, float* out, int layout_g, int* n_parts, float* ws, int64_t ws_floats,
                        int* tile_cnt, int n_cu, int sched, const float* row_scale, const float* col_scale,
-                       int* used, int* n_sub) {
+                       int* used, int* n_sub, const char** kernel) {
   *n_sub = 1;
 #define MHC_GEMM(P) \
   launch_gemm_prec<P>(s, E, B, M_pad, K_pad, ntb, out, layout_g, n_parts, ws, ws_floats, tile_cnt, n_cu, sched, \
-                      row_scale, col_scale, used, n_sub)
+                      row_scale, col_scale, used, n_sub, kernel)
   switch (prec) {
     case PREC_BF16X3: return MHC_GEMM(PREC_BF16X3);
     case PREC_FP8: return MHC_GEMM(PREC_FP8);
@@ -1535,7 +1542,7 @@ hipError_t launch_gemm(hipStream_t s, int prec, const void* E, const void* B, in
 
 template <int PREC, int WM, int WT, int MB, bool TR>
 static hipError_t launch_dir_shape(hipStream_t s, GemmGeom g, int s3, int64_t region, float* ws, int64_t ws_floats,
-                                   int n_cu, int* n_sub) {
+                                   int n_cu, int sched, int* n_sub, const char** kernel) {
   constexpr int NBR = MB * 3 * 16;
   const int64_t n_tiles = (g.M_pad / (WM * MB * 32)) * g.n_ntiles;
   const int64_t G = std::min<int64_t>({n_tiles, (int64_t)n_cu, ws_floats / ((int64_t)2 * NBR * 256)});
@@ -1544,10 +1551,13 @@ static hipError_t launch_dir_shape(hipStream_t s, GemmGeom g, int s3, int64_t re
   g.region = region;
   g.ws = ws;
   const int64_t units = n_tiles * WM * MB * WT;
-  if (chan_us(PREC, units, g.n_stages, n_cu) < tile_us(PREC, (double)((n_tiles + G - 1) / G) * g.n_stages, MB, 1)) {
+  if (sched == MHC_SCHED_AUTO &&
+      chan_us(PREC, units, g.n_stages, n_cu) < tile_us(PREC, (double)((n_tiles + G - 1) / G) * g.n_stages, MB, 1)) {
+    *kernel = "k_gemm_chan";
     *n_sub = TR ? WT : 1;
     return launch_chan<PREC, TR, 2>(s, g, SplitPlan{}, ChanTiles{0, WM * MB, WT}, n_tiles, n_cu);
   }
+  *kernel = "k_gemm_dir";
   hipLaunchKernelGGL((k_gemm_dir<PREC, WM, WT, MB, TR>), dim3((unsigned)G), dim3(256), 0, s, g);
   return hipGetLastError();
 }
@@ -1555,8 +1565,8 @@ static hipError_t launch_dir_shape(hipStream_t s, GemmGeom g, int s3, int64_t re
 template <int PREC>
 static hipError_t launch_gemm_dir_prec(hipStream_t s, const void* E, const void* B, int64_t M_pad, int64_t n3, int ntb,
                                        float* out, int64_t region, int layout_g, int* n_parts, float* ws,
-                                       int64_t ws_floats, int n_cu, const float* row_scale, const float* col_scale,
-                                       int* n_sub) {
+                                       int64_t ws_floats, int n_cu, int sched, const float* row_scale,
+                                       const float* col_scale, int* n_sub, const char** kernel) {
   constexpr int SD = stage_dofs(PREC);
   if (n3 % SD != 0) return hipErrorInvalidValue;
   GemmGeom g{};
@@ -1572,8 +1582,8 @@ static hipError_t launch_gemm_dir_prec(hipStream_t s, const void* E, const void*
   g.col_scale = col_scale;
   const int s3 = (int)(n3 / SD);
 #define MHC_DSHAPE(WM, WT, MB)                                                                           \
-  (layout_g ? launch_dir_shape<PREC, WM, WT, MB, false>(s, g, s3, region, ws, ws_floats, n_cu, n_sub)     \
-            : launch_dir_shape<PREC, WM, WT, MB, true>(s, g, s3, region, ws, ws_floats, n_cu, n_sub))
+  (layout_g ? launch_dir_shape<PREC, WM, WT, MB, false>(s, g, s3, region, ws, ws_floats, n_cu, sched, n_sub, kernel)     \
+            : launch_dir_shape<PREC, WM, WT, MB, true>(s, g, s3, region, ws, ws_floats, n_cu, sched, n_sub, kernel))
   if (ntb % 4 == 0) {
     g.n_ntiles = ntb / 4;
     *n_parts = g.n_ntiles;
@@ -1591,12 +1601,13 @@ static hipError_t launch_gemm_dir_prec(hipStream_t s, const void* E, const void*
 
 hipError_t launch_gemm_dir(hipStream_t s, int prec, const void* E, const void* B, int64_t M_pad, int64_t n3, int ntb,
                            float* out, int64_t region, int layout_g, int* n_parts, float* ws, int64_t ws_floats,
-                           int n_cu, const float* row_scale, const float* col_scale, int* n_sub) {
+                           int n_cu, int sched, const float* row_scale, const float* col_scale, int* n_sub,
+                           const char** kernel) {
   if (n3 <= 0) return hipErrorInvalidValue;
   *n_sub = 1;
 #define MHC_DIRP(P) \
-  launch_gemm_dir_prec<P>(s, E, B, M_pad, n3, ntb, out, region, layout_g, n_parts, ws, ws_floats, n_cu, row_scale, \
-                          col_scale, n_sub)
+  launch_gemm_dir_prec<P>(s, E, B, M_pad, n3, ntb, out, region, layout_g, n_parts, ws, ws_floats, n_cu, sched, \
+                          row_scale, col_scale, n_sub, kernel)
   switch (prec) {
     case PREC_BF16X3: return MHC_DIRP(PREC_BF16X3);
     case PREC_FP8: return MHC_DIRP(PREC_FP8);

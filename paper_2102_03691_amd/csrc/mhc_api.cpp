@@ -206,6 +206,7 @@ struct mhc_ctx {
   float* d_ws = nullptr;      // partial tiles of the split and stream-K schedules
   int* d_tile_cnt = nullptr;  // arrival counters of the split schedule (zero between launches)
   int* d_flag = nullptr;      // non-finite flag of the device-input check
+  const char* last_kernel = "";   // contraction kernel of the last pushed block
   int last_sched = 0;         // schedule the last batched contraction used (MHC_SCHED_*; 0 = none yet)
   int64_t ws_floats = 0;
   int n_cu = 256;
@@ -1017,8 +1018,8 @@ static mhc_status run_block(mhc_ctx* ctx, const float* v, const float* W, int t_
     if (timed && (st = timing_begin(ctx, &e0, &e1))) return st;
     int n_parts = 0, n_sub = 1;
     HIP_TRY(launch_gemm_dir(ctx->stream, c.precision, ctx->dE, ctx->dB, ctx->M_pad, ctx->n3, ctx->t_pad / 32, ctx->dJ,
-                            ctx->j_region, gk ? 1 : 0, &n_parts, wk.ws, wk.ws_floats, ctx->n_cu, ctx->d_rowscale,
-                            ctx->d_colscale, &n_sub),
+                            ctx->j_region, gk ? 1 : 0, &n_parts, wk.ws, wk.ws_floats, ctx->n_cu, c.schedule,
+                            ctx->d_rowscale, ctx->d_colscale, &n_sub, &ctx->last_kernel),
             "direction-split contraction");
     ctx->last_sched = MHC_SCHED_TILES;
     if (e1) HIP_TRY(hipEventRecord(e1, ctx->stream), "event record");
@@ -1038,19 +1039,19 @@ static mhc_status run_block(mhc_ctx* ctx, const float* v, const float* W, int t_
     if (small) {
       HIP_TRY(launch_gemv_small(ctx->stream, reinterpret_cast<const float*>(ctx->dE), v, W, ctx->d_sqrtm, ctx->d_isqrtm,
                                 ctx->N, t_count, ctx->M_pad, ctx->K_pad, ctx->dJ, gk ? 1 : 0, ctx->t_pad, ctx->d_jt,
-                                ctx->n_atom_chunks, ctx->t_pad),
+                                ctx->n_atom_chunks, ctx->t_pad, &ctx->last_kernel),
               "per-step input prep and contraction");
       n_parts = t_count;
     } else if (c.t_block == 1) {
       HIP_TRY(launch_gemv_f32(ctx->stream, reinterpret_cast<const float*>(ctx->dE),
                               reinterpret_cast<const float*>(ctx->dB), t_count, ctx->M_pad, ctx->K_pad, ctx->dJ,
-                              gk ? 1 : 0, ctx->t_pad),
+                              gk ? 1 : 0, ctx->t_pad, &ctx->last_kernel),
               "per-step contraction");
       n_parts = t_count;
     } else {
       HIP_TRY(launch_gemm(ctx->stream, c.precision, ctx->dE, ctx->dB, ctx->M_pad, ctx->K_pad, ctx->t_pad / 32,
                           ctx->dJ, gk ? 1 : 0, &n_parts, wk.ws, wk.ws_floats, wk.cnt, ctx->n_cu, c.schedule,
-                          ctx->d_rowscale, ctx->d_colscale, &ctx->last_sched, &n_sub),
+                          ctx->d_rowscale, ctx->d_colscale, &ctx->last_sched, &n_sub, &ctx->last_kernel),
               "batched contraction");
     }
     if (e1) HIP_TRY(hipEventRecord(e1, ctx->stream), "event record");
@@ -1580,6 +1581,8 @@ mhc_status mhc_device_bytes(mhc_ctx* ctx, int64_t* bytes) {
   *bytes = ctx->bytes;
   return MHC_OK;
 }
+
+const char* mhc_last_kernel(const mhc_ctx* ctx) { return ctx ? ctx->last_kernel : ""; }
 
 mhc_status mhc_last_schedule(mhc_ctx* ctx, int32_t* schedule) {
   if (!ctx || !schedule) return MHC_ERR_INVALID_ARG;

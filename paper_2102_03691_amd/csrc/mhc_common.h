@@ -88,15 +88,17 @@ hipError_t launch_nonfinite(hipStream_t s, const float* p, int64_t n, int* flag)
 // B buffer, J_n^mu = Xdot_n A_n^mu for every slot.  Output either
 //   hnema: out[t][M_pad][3]   (layout_g == 0)
 //   gkma : out[3][M_pad][ld]  at column t (layout_g == 1)
+// Every contraction launcher names the kernel it launched through *kernel
+// (static string).
 hipError_t launch_gemv_f32(hipStream_t s, const float* E, const float* B, int n_steps, int64_t M_pad,
-                           int64_t K_pad, float* out, int layout_g, int64_t ld);
+                           int64_t K_pad, float* out, int layout_g, int64_t ld, const char** kernel);
 
 // The same for few waves and a small operand (gemv_small), straight from the
 // inputs: no input prep, the Eq. 10 partials come from this launch.
 bool gemv_small(int n_steps, int64_t M_pad, int64_t K_pad);
 hipError_t launch_gemv_small(hipStream_t s, const float* E, const float* v, const float* W, const float* sqrt_m,
                              const float* inv_sqrt_m, int64_t N, int n_steps, int64_t M_pad, int64_t K_pad, float* out,
-                             int layout_g, int64_t ld, double* jt_part, int n_chunks, int t_pad);
+                             int layout_g, int64_t ld, double* jt_part, int n_chunks, int t_pad, const char** kernel);
 
 // Geometry of one system's T-batched contraction (plain data, shared with
 // the grouped launch, which keeps an array of these in device memory).
@@ -143,7 +145,9 @@ hipError_t launch_fill_i32(hipStream_t s, int* p, int n, int v);
 //   hnema:  out[ntile][M_pad][3]   sum over the tile's steps
 //   gkma :  out[3][M_pad][t_pad]
 //   ws      stream-K workspace (ws_floats floats); n_cu = compute units
-//   sched   0 = automatic, 1 = one tile per work-group, 2 = stream-K
+//   sched   MHC_SCHED_*; what ran is returned through *used.  With AUTO a launch
+//           of few tiles computes the same sums one channel per wave
+//           (k_gemm_chan) and *used is the split whose sums they are
 // Returns the number of column tiles through *n_parts, and through *n_sub the
 // number of float32 sums each hnema part is written as: out[ntile][n_sub]
 // [M_pad][3], one per t-block where the t-blocks of a tile ran apart (the
@@ -151,7 +155,7 @@ hipError_t launch_fill_i32(hipStream_t s, int* p, int n, int v);
 hipError_t launch_gemm(hipStream_t s, int prec, const void* E, const void* B, int64_t M_pad,
                        int64_t K_pad, int ntb, float* out, int layout_g, int* n_parts, float* ws,
                        int64_t ws_floats, int* tile_cnt, int n_cu, int sched, const float* row_scale,
-                       const float* col_scale, int* used, int* n_sub);
+                       const float* col_scale, int* used, int* n_sub, const char** kernel);
 
 // Motion-direction split as one contraction: K ordered direction-major
 // (third nu = dofs (i, nu) at k = nu*n3 + i, n3 a multiple of the precision's
@@ -159,10 +163,12 @@ hipError_t launch_gemm(hipStream_t s, int prec, const void* E, const void* B, in
 // nu at out + nu * region), each laid out as launch_gemm's out.  ws holds two
 // bracket slots per work-group (ws_floats floats); n_cu = compute units;
 // row_scale / col_scale as for launch_gemm (e4m3; whole-column activation
-// scales, the same for every third); n_sub as for launch_gemm.
+// scales, the same for every third); n_sub as for launch_gemm.  sched: with
+// AUTO a launch of few tiles runs one channel per wave (k_gemm_chan).
 hipError_t launch_gemm_dir(hipStream_t s, int prec, const void* E, const void* B, int64_t M_pad, int64_t n3, int ntb,
                            float* out, int64_t region, int layout_g, int* n_parts, float* ws, int64_t ws_floats,
-                           int n_cu, const float* row_scale, const float* col_scale, int* n_sub);
+                           int n_cu, int sched, const float* row_scale, const float* col_scale, int* n_sub,
+                           const char** kernel);
 
 // dofs per k-stage of a precision's T-batched contraction.
 int stage_dofs_of(int prec);
