@@ -322,7 +322,26 @@ hipError_t launch_gemv_small(hipStream_t s, const float* E, const float* v, cons
 // accumulators per exchange (each half-wave keeps one and sends the other;
 // a + b = b + a).  Measured, 4096 atoms, 64 steps: 5696 -> 1190 us.
 constexpr int GEMV_TS = 4;
-constexpr int64_t GEMV_STEPS_MIN_UNITS = 1024;   // 256 CUs x 4 SIMDs
+
+// Which of the two.  A round is one wave of k_gemv_f32 per SIMD (256 CUs x 4),
+// a unit one such wave; the steps kernel takes one time per operand length
+// while a CU has at most one of its work-groups.  One round: k_gemv_f32 is
+// always ahead.  From the fourth on it is behind everywhere.  Between, it is
+// ahead as long as its own waits are short: short operands, and a basis that
+// the L2s keep while the steps re-read it, with few activations beside it (not
+// 64 steps of 256 modes).  Measured, k_gemv_f32 / k_gemv_steps in us,
+// dofs x modes, steps: two rounds 4608 x 1024, 11: 24 / 33; 6144 x 1024, 13: 32
+// / 41; 8704 x 1536, 7: 55 / 55; 8704 x 2048, 6: 58 / 55; 4608 x 3072, 4: 35 /
+// 33; 12288 x 4096, 4: 102 / 74; 24064 x 512, 21: 142 / 137; three rounds 1536 x
+// 512, 42: 14 / 17; 3072 x 1536, 14: 24 / 25; 3072 x 2048, 11: 28 / 25; 3072 x
+// 256, 84: 28 / 25; 4608 x 512, 42: 38 / 33.
+static bool gemv_steps(int n_steps, int64_t M_pad, int64_t K_pad) {
+  const int64_t units = M_pad / GEMV_ROWS * n_steps;
+  if (units <= 1024) return false;
+  if (units <= 2048) return M_pad >= 3072 || M_pad * K_pad >= (int64_t(16) << 20) || K_pad >= 16384;
+  if (units <= 3072) return K_pad > 4096 || M_pad >= 2048 || (n_steps > 64 && K_pad >= 3072);
+  return true;
+}
 
 __global__ void __launch_bounds__(256, 2)
 k_gemv_steps(const f32x4* __restrict__ E, const float* __restrict__ B, int n_steps, int64_t M_pad, int64_t K_pad,
@@ -426,11 +445,7 @@ hipError_t launch_gemv_f32(hipStream_t s, const float* E, const float* B, int n_
   if (n_steps <= 0) return hipSuccess;
   if (M_pad % M_ALIGN != 0 || K_pad % K_ALIGN_GEMV != 0) return hipErrorInvalidValue;
   const int64_t units = (M_pad / GEMV_ROWS) * n_steps;
-  // One pass over E for up to four steps, where the waves of one step each
-  // would be more than one per SIMD: below that E is read by idle CUs anyway
-  // and the longer waves are slower (1000 atoms: 2 steps 18.0 -> 25.5 us, 3
-  // steps 27.2 -> 25.2 us, 16 steps 64 -> 32 us).
-  if (units > GEMV_STEPS_MIN_UNITS && n_steps >= 2) {
+  if (n_steps >= 2 && gemv_steps(n_steps, M_pad, K_pad)) {
     const int64_t wgs = (M_pad / (4 * GEMV_ROWS)) * ((n_steps + GEMV_TS - 1) / GEMV_TS);
     if (wgs > INT32_MAX) return hipErrorInvalidValue;
     *kernel = "k_gemv_steps";
