@@ -74,55 +74,64 @@ struct DevBuf {
 };
 
 // Pinned read-out buffers: allocations of 16, with the ones in use as bits.
-struct PinnedSlab {
-  char* base = nullptr;
-  uint32_t used = 0;
-};
 constexpr int kSlabBuffers = 16;
+struct PinnedSlab {
+  char* base;
+  uint32_t used;
+  PinnedSlab* next;
+};
 std::mutex g_pinned_mu;
-std::vector<PinnedSlab>& pinned_slabs() {   // never destroyed: objects may outlive the statics
-  static auto* slabs = new std::vector<PinnedSlab>();
-  return *slabs;
-}
+PinnedSlab* g_pinned = nullptr;
 
 }  // namespace
 
 namespace mhc {
 
-double* pinned_acquire() {
+double* pinned_acquire(bool allocate) {
   std::lock_guard<std::mutex> lock(g_pinned_mu);
-  auto& slabs = pinned_slabs();
-  auto it = std::find_if(slabs.begin(), slabs.end(),
-                         [](const PinnedSlab& s) { return s.used != (1u << kSlabBuffers) - 1; });
-  if (it == slabs.end()) {
+  PinnedSlab* s = g_pinned;
+  while (s && s->used == (1u << kSlabBuffers) - 1) s = s->next;
+  if (!s) {
+    if (!allocate || !(s = new (std::nothrow) PinnedSlab{})) return nullptr;
+    // allowed while another thread captures a graph (this thread's mode, and back)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     void* p = nullptr;
-    if (hipHostMalloc(&p, kSlabBuffers * kPinnedBytes, hipHostMallocPortable) != hipSuccess) {
+    const hipError_t e = hipHostMalloc(&p, kSlabBuffers * kPinnedBytes, hipHostMallocPortable);
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
       (void)hipGetLastError();
+      delete s;
       return nullptr;
     }
-    slabs.push_back({static_cast<char*>(p), 0});
-    it = slabs.end() - 1;
+    s->base = static_cast<char*>(p);
+    s->next = g_pinned;
+    g_pinned = s;
   }
-  int k = 0;
-  while (it->used >> k & 1) ++k;
-  it->used |= 1u << k;
-  return reinterpret_cast<double*>(it->base + k * kPinnedBytes);
+  const int k = __builtin_ctz(~s->used);
+  s->used |= 1u << k;
+  return reinterpret_cast<double*>(s->base + k * kPinnedBytes);
 }
 
 void pinned_release(double* buffer) {
   if (!buffer) return;
   std::lock_guard<std::mutex> lock(g_pinned_mu);
-  auto& slabs = pinned_slabs();
   const char* p = reinterpret_cast<const char*>(buffer);
-  for (auto it = slabs.begin(); it != slabs.end(); ++it) {
-    if (p < it->base || p >= it->base + kSlabBuffers * kPinnedBytes) continue;
-    it->used &= ~(1u << ((p - it->base) / kPinnedBytes));
-    if (!it->used) {
-      (void)hipHostFree(it->base);
-      slabs.erase(it);
-    }
-    return;
-  }
+  PinnedSlab** at = &g_pinned;
+  while (*at && !(p >= (*at)->base && p < (*at)->base + kSlabBuffers * kPinnedBytes)) at = &(*at)->next;
+  PinnedSlab* s = *at;
+  if (!s) return;
+  s->used &= ~(1u << ((p - s->base) / kPinnedBytes));
+  if (s->used) return;
+  *at = s->next;
+  (void)hipHostFree(s->base);
+  delete s;
+}
+
+double* PinnedReads::buffer(size_t bytes) {
+  if (bytes > kPinnedBytes) return nullptr;
+  if (!buf) buf = pinned_acquire(n_reads++ > 0);
+  return buf;
 }
 
 }  // namespace mhc
@@ -202,7 +211,7 @@ struct mhc_ctx {
   int64_t R3 = 0;
   double *d_csum = nullptr, *d_ccomp = nullptr;
   double* d_out = nullptr;
-  double* h_out = nullptr;    // pinned, kPinnedBytes: small read-outs
+  PinnedReads reads;          // small read-outs
   float* d_ws = nullptr;      // partial tiles of the split and stream-K schedules
   int* d_tile_cnt = nullptr;  // arrival counters of the split schedule (zero between launches)
   int* d_flag = nullptr;      // non-finite flag of the device-input check
@@ -279,8 +288,7 @@ void rollback_allocs(mhc_ctx* c, size_t mark) {
 }
 
 void free_all(mhc_ctx* c) {
-  pinned_release(c->h_out);
-  c->h_out = nullptr;
+  c->reads.release();
   for (auto& a : c->allocs) (void)hipFree(a.p);
   c->allocs.clear();
   c->bytes = 0;
@@ -744,8 +752,6 @@ static mhc_status finalize_impl(mhc_ctx* ctx) {
     }
   }
   if ((st = dev_alloc(ctx, out_doubles * 8, &pout, "read-out"))) return st;
-  if (!ctx->h_out && !(ctx->h_out = pinned_acquire()))
-    return fail(ctx, MHC_ERR_OOM, "pinned allocation failed: read-out");
   void* pflag = nullptr;
   if ((st = dev_alloc(ctx, 16, &pflag, "non-finite flag"))) return st;
   ctx->d_flag = reinterpret_cast<int*>(pflag);
@@ -1213,32 +1219,26 @@ mhc_status mhc_synchronize(mhc_ctx* ctx) {
   return MHC_OK;
 }
 
-// Finished HNEMA averages on the host: h[0 .. nd*nb*3) = bin averages
-// [dir][b][mu], then the Eq. 10 total [3], then (split) the split totals [dir][mu].
-// Small read-outs are written by the finishing kernel straight into the
-// context's pinned buffer (host memory that the GPU writes over PCIe): one
-// kernel and one synchronization, no copy (a push and HNEMA read of a 64-atom
-// system: 75 us with two kernels and two copies into pageable memory, 38 us
-// now).  Larger ones go through d_out: 64 KB at PCIe rate is about what a copy
-// costs to start.
-static bool reads_pinned(size_t doubles) { return doubles * 8 <= kPinnedBytes; }
-
-// Finished HNEMA averages on the host: *h = bins [dir][nb][3], total [3], split
+// Finished HNEMA averages on the host: *out = bins [dir][nb][3], total [3], split
 // totals [dir][3] (valid until the next call on the context).
+// Small read-outs are written by the finishing kernel straight into the
+// context's pinned buffer (host memory that the GPU writes over PCIe), if it has
+// one: one kernel and one synchronization, no copy.  Larger ones go through
+// d_out: 64 KB at PCIe rate is about what a copy costs to start.
 static mhc_status hnema_finished(mhc_ctx* ctx, const double** out, std::vector<double>& h) {
   const int nd = ctx->n_dir;
   const int64_t n = (int64_t)nd * ctx->nb * 3;
   const size_t all = n + 3 + (nd > 1 ? 9 : 0);
-  const bool pinned = reads_pinned(all);
+  double* const pinned = ctx->reads.buffer(all * 8);
   HIP_TRY(launch_hnema_finish(ctx->stream, ctx->d_hsum, ctx->d_hcomp, n, ctx->d_tsum, ctx->d_tcomp, ctx->d_tdsum,
-                              ctx->d_tdcomp, ctx->n_samples, pinned ? ctx->h_out : ctx->d_out),
+                              ctx->d_tdcomp, ctx->n_samples, pinned ? pinned : ctx->d_out),
           "finish");
   if (!pinned) {
     h.resize(all);
     HIP_TRY(hipMemcpyAsync(h.data(), ctx->d_out, all * 8, hipMemcpyDeviceToHost, ctx->stream), "read");
   }
   HIP_TRY(hipStreamSynchronize(ctx->stream), "read sync");
-  *out = pinned ? ctx->h_out : h.data();
+  *out = pinned ? pinned : h.data();
   return MHC_OK;
 }
 
@@ -1303,8 +1303,9 @@ static mhc_status gkma_finished(mhc_ctx* ctx, int d, const double** out, bool* h
     psum = ctx->d_psum;
     pcomp = ctx->d_psum + per;
   }
-  *host = reads_pinned(2 * n + (size_t)L * 9);
-  double* o = *host ? ctx->h_out : ctx->d_out;
+  double* const pinned = ctx->reads.buffer((2 * n + (size_t)L * 9) * 8);
+  *host = pinned != nullptr;
+  double* o = pinned ? pinned : ctx->d_out;
   HIP_TRY(launch_corr_finish(ctx->stream, ctx->d_csum + d * per, ctx->d_ccomp + d * per, psum, pcomp, ctx->nb, L,
                              ctx->n_samples, ctx->cfg.dt, o, o + n, o + 2 * n),
           "finish");

@@ -231,13 +231,30 @@ hipError_t launch_corr(hipStream_t s, const double* X, int64_t ldx, int t_count,
                        int64_t out_zs = 0);
 
 // A pinned host buffer of kPinnedBytes for the small read-outs of one object
-// (null when the allocation fails), and its return.  Sixteen buffers to an
-// allocation, which is freed with its last one: hipHostMalloc takes 30 to 130
-// us whatever the size, hipHostFree 120 us.  From any thread; the owner returns
-// a buffer after its stream has drained.
+// (null when there is none: the allocation failed, or allocate = false and no
+// buffer of an allocation made before is free), and its return.  Sixteen
+// buffers to an allocation, which is freed with its last one: hipHostMalloc
+// takes 30 to 130 us whatever the size, hipHostFree 50 to 120 us.  From any
+// thread; the owner returns a buffer after its stream has drained.
 constexpr size_t kPinnedBytes = size_t(64) << 10;
-double* pinned_acquire();
+double* pinned_acquire(bool allocate);
 void pinned_release(double* buffer);
+
+// The pinned buffer of one object's reads.  A first read takes one that is
+// there, or none (the copy makes it 8 us longer); the allocation comes with the
+// second, so that an object that is made, read once and destroyed, the only one
+// of its process, does not pay for it (a per-step context of 64 atoms from
+// create to destroy 207 us, with the allocation in finalize 260; an SHC object
+// of 216 atoms 105 and 122 us).
+struct PinnedReads {
+  double* buf = nullptr;
+  int64_t n_reads = 0;   // of those that found no buffer
+  double* buffer(size_t bytes);   // null: copy from device memory
+  void release() {
+    pinned_release(buf);
+    buf = nullptr;
+  }
+};
 
 // Read-out of the GKMA accumulators: C = (csum + ccomp [+ psum + pcomp]) /
 // (S - tau) (zero when S <= tau; psum, pcomp optional: the correlation of

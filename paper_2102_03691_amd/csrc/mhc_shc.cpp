@@ -47,7 +47,7 @@ struct mhc_shc {
   double* part = nullptr;              // [3 n_kcs][T/64][n_lags_pad][3]
   double* ksum = nullptr;              // [3 nu][n_lags][3 mu] x 2 (sum, compensation)
   double* kout = nullptr;              // [n_lags][3] then [n_lags][3][3] read-out
-  double* h_out = nullptr;             // pinned, kPinnedBytes: small read-outs and the frequencies asked for
+  PinnedReads reads;                   // small read-outs and the frequencies asked for
   double* omega = nullptr;             // spectrum frequencies (grown on demand)
   double* kw = nullptr;                // [n_omega][3]
   int omega_cap = 0;
@@ -107,8 +107,7 @@ void sfree(mhc_shc* c) {
   }
   for (void* p : c->allocs) (void)hipFree(p);
   c->allocs.clear();
-  pinned_release(c->h_out);
-  c->h_out = nullptr;
+  c->reads.release();
   for (auto e : c->ev) (void)hipEventDestroy(e);
   c->ev.clear();
   for (hipEvent_t* e : {&c->ev_start, &c->ev_copied[0], &c->ev_copied[1], &c->ev_free[0], &c->ev_free[1]})
@@ -218,7 +217,6 @@ mhc_status mhc_shc_create(int device, void* hip_stream, int64_t n_atoms, int32_t
       salloc(c, (size_t)3 * c->n_kcs * (t_block / 64) * lags_pad(n_lags) * 3 * 8, &pp, "partials") ||
       salloc(c, (size_t)n_lags * (9 * 2 + 12) * 8, &ps, "sums and read-out"))
     return bail(MHC_ERR_OOM, "device allocation failed");
-  if (!(c->h_out = pinned_acquire())) return bail(MHC_ERR_OOM, "pinned allocation failed");
   c->ring = static_cast<float*>(pr);
   c->vt = static_cast<float*>(pvt);
   c->sv = static_cast<float*>(pv);
@@ -327,8 +325,8 @@ static mhc_status shc_read(mhc_shc* c, double* K, int64_t* n_samples, int split)
   if (!K) return sfail(c, MHC_ERR_INVALID_ARG, "NULL output");
   const size_t n = (size_t)c->n_lags * 3, bytes = (split ? 3 : 1) * n * 8;
   // written by the kernel into the pinned buffer where it fits: no copy
-  const bool pinned = bytes <= kPinnedBytes;
-  double* o = pinned ? c->h_out : c->kout;
+  double* const pinned = c->reads.buffer(bytes);
+  double* o = pinned ? pinned : c->kout;
   SHIP_TRY(launch_shc_finish(c->stream, c->ksum, c->ksum + 9 * c->n_lags, c->n_lags, c->S, split ? nullptr : o,
                              split ? o : nullptr),
            "finish");
@@ -355,7 +353,7 @@ static mhc_status shc_spectrum(mhc_shc* c, int32_t n_omega, const double* omega,
   const size_t n = (size_t)c->n_lags * 3;
   const int nc = split ? 9 : 3;
   // frequencies and results through the pinned buffer where they fit
-  const bool pinned = (size_t)n_omega * (1 + nc) * 8 <= kPinnedBytes;
+  double* const pinned = c->reads.buffer((size_t)n_omega * (1 + nc) * 8);
   if (!pinned && n_omega > c->omega_cap) {
     void *po, *pk;
     if ((st = salloc(c, (size_t)n_omega * 8, &po, "frequencies"))) return st;
@@ -364,8 +362,8 @@ static mhc_status shc_spectrum(mhc_shc* c, int32_t n_omega, const double* omega,
     c->kw = static_cast<double*>(pk);
     c->omega_cap = n_omega;
   }
-  double* om = pinned ? c->h_out : c->omega;
-  double* kw = pinned ? c->h_out + n_omega : c->kw;
+  double* om = pinned ? pinned : c->omega;
+  double* kw = pinned ? pinned + n_omega : c->kw;
   if (pinned) std::memcpy(om, omega, (size_t)n_omega * 8);
   else
     SHIP_TRY(hipMemcpyAsync(om, omega, (size_t)n_omega * 8, hipMemcpyHostToDevice, c->stream), "copy omega");

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/mhc.h"
+#include "mhc_common.h"
 #include "mhc_tersoff.h"
 
 using namespace mhc;
@@ -41,8 +42,8 @@ struct mhc_virial {
   CellGrid cg{};
   bool lists_ok = false;
 
-  std::vector<void*> allocs;
-  void* h_read = nullptr;   // 64 bytes of pinned memory: the search's flags (last 16), bond flags and thermostat read back
+  void* mem = nullptr;      // the device buffers below, one allocation
+  double* h_read = nullptr; // pinned, 64 bytes of it: bond flags and thermostat read back, the search's flags (last 16)
   double* d_mass = nullptr;
   NeighborBufs nb{};
   double *d_dd = nullptr, *d_U = nullptr;
@@ -127,23 +128,23 @@ mhc_status venter(mhc_virial* v) {
 }
 
 void vfree(mhc_virial* v) {
-  for (void* p : v->allocs) (void)hipFree(p);
-  v->allocs.clear();
-  if (v->h_read) (void)hipHostFree(v->h_read);
+  if (v->mem) (void)hipFree(v->mem);
+  v->mem = nullptr;
+  pinned_release(v->h_read);
   v->h_read = nullptr;
 }
 
-template <class T>
-bool valloc(mhc_virial* v, size_t count, T** out) {
-  void* p = nullptr;
-  if (hipMalloc(&p, std::max<size_t>(count * sizeof(T), 16)) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
+// Parts of one device allocation (a hipMalloc and hipFree each for two dozen
+// took 15 us longer an object); base null: sizes only.
+struct Parts {
+  char* base = nullptr;
+  size_t bytes = 0;
+  template <class T>
+  void take(size_t count, T** out) {
+    if (base) *out = reinterpret_cast<T*>(base + bytes);
+    bytes += (std::max<size_t>(count * sizeof(T), 1) + 255) / 256 * 256;
   }
-  v->allocs.push_back(p);
-  *out = reinterpret_cast<T*>(p);
-  return true;
-}
+};
 
 bool finite_params(const mhc_tersoff_params* p) {
   const double x[] = {p->A, p->B, p->lambda1, p->lambda2, p->lambda3, p->beta, p->n, p->c, p->d, p->h, p->gamma,
@@ -246,24 +247,28 @@ mhc_status mhc_virial_create(int device, void* hip_stream, int64_t n_atoms, cons
   const int64_t N = n_atoms, MN = (int64_t)max_neighbors * N;
   const int64_t n_cells = (int64_t)v->cg.nc[0] * v->cg.nc[1] * v->cg.nc[2];
   NeighborBufs& b = v->nb;
-  bool ok = valloc(v, N, &v->d_mass) && valloc(v, MN, &b.nbr) && valloc(v, MN, &b.rev) && valloc(v, N, &b.n_nb) &&
-            valloc(v, N, &b.cell_of) && valloc(v, N, &b.place) && valloc(v, N, &b.atoms) &&
-            valloc(v, 3 * N, &b.cpos) && valloc(v, n_cells, &b.count) && valloc(v, n_cells + 1, &b.start) &&
-            valloc(v, (n_cells + 1023) / 1024, &b.tile_sums) && valloc(v, (N + 15) / 16, &b.most) &&
-            valloc(v, 3 * MN, &v->d_dd) && valloc(v, N, &v->d_U) && valloc(v, 3 * N, &v->d_F) &&
-            valloc(v, 8, &v->d_thermo) && valloc(v, 3 * N, &v->d_pos2) &&
-            valloc(v, std::max(md_nvt_parts(N), gather_parts(N, 64)), &v->d_kepart) &&
-            valloc(v, MN, &v->bb.nbr) && valloc(v, MN, &v->bb.rev) && valloc(v, N, &v->bb.n_nb) &&
-            valloc(v, N, &v->bb.mask) && valloc(v, 3 * N, &v->bb.ref) && valloc(v, 12, &v->bb.flags);
-  if (!ok) return cleanup(MHC_ERR_OOM, "device allocation failed");
-  if (hipHostMalloc(reinterpret_cast<void**>(&v->h_read), 64) != hipSuccess) {
+  auto carve = [&](char* base) {
+    Parts m{base};
+    m.take(N, &v->d_mass), m.take(MN, &b.nbr), m.take(MN, &b.rev), m.take(N, &b.n_nb);
+    m.take(N, &b.cell_of), m.take(N, &b.place), m.take(N, &b.atoms), m.take(3 * N, &b.cpos);
+    m.take(n_cells, &b.count), m.take(n_cells + 1, &b.start), m.take((n_cells + 1023) / 1024, &b.tile_sums);
+    m.take((N + 15) / 16, &b.most);
+    m.take(3 * MN, &v->d_dd), m.take(N, &v->d_U), m.take(3 * N, &v->d_F), m.take(8, &v->d_thermo);
+    m.take(3 * N, &v->d_pos2), m.take(std::max(md_nvt_parts(N), gather_parts(N, 64)), &v->d_kepart);
+    m.take(MN, &v->bb.nbr), m.take(MN, &v->bb.rev), m.take(N, &v->bb.n_nb), m.take(N, &v->bb.mask);
+    m.take(3 * N, &v->bb.ref), m.take(12, &v->bb.flags);
+    return m.bytes;
+  };
+  if (hipMalloc(&v->mem, carve(nullptr)) != hipSuccess) {
     (void)hipGetLastError();
-    v->h_read = nullptr;
-    return cleanup(MHC_ERR_OOM, "pinned allocation failed");
+    v->mem = nullptr;
+    return cleanup(MHC_ERR_OOM, "device allocation failed");
   }
+  (void)carve(static_cast<char*>(v->mem));
+  if (!(v->h_read = pinned_acquire(true))) return cleanup(MHC_ERR_OOM, "pinned allocation failed");
   // the search's kernels write their three results straight into the last 16
   // bytes of the pinned buffer: no copy behind the search
-  b.flags = static_cast<int*>(v->h_read) + 12;
+  b.flags = reinterpret_cast<int*>(v->h_read) + 12;
   v->bb.need = v->bb.flags + 8;
   v->bond_skin = std::min(rc - (p.R + p.D), 0.5);
   if (launch_zero_i32(v->stream, b.count, (int)n_cells) != hipSuccess ||
@@ -543,7 +548,7 @@ mhc_status md_run(mhc_virial* v, double* pos, double* vel, double dt, int32_t n_
   }
   if (F) VHIP_TRY(hipMemcpyAsync(F, v->d_F, (size_t)N * 3 * 8, hipMemcpyDeviceToDevice, v->stream), "copy forces");
   if (any_compact) {
-    const int* f = static_cast<const int*>(v->h_read);
+    const int* f = reinterpret_cast<const int*>(v->h_read);
     VHIP_TRY(hipMemcpyAsync(v->h_read, v->bb.flags, 3 * sizeof(int), hipMemcpyDeviceToHost, v->stream), "read bond flags");
     VHIP_TRY(hipStreamSynchronize(v->stream), "md sync");
     if (f[1])
@@ -554,7 +559,7 @@ mhc_status md_run(mhc_virial* v, double* pos, double* vel, double dt, int32_t n_
     if (f[2]) return vfail(v, MHC_ERR_INVALID_ARG, "bond lists are not symmetric (non-finite positions?)");
   }
   if (nvt) {
-    const double* th = static_cast<const double*>(v->h_read);
+    const double* th = v->h_read;
     VHIP_TRY(hipMemcpyAsync(v->h_read, th_now, 4 * sizeof(double), hipMemcpyDeviceToHost, v->stream), "read thermostat");
     VHIP_TRY(hipStreamSynchronize(v->stream), "md sync");
     nvt->state[0] = th[0];
