@@ -548,8 +548,8 @@ typedef struct {
  * in [1, 64] (atoms within R + D + skin); skin >= 0 widens the neighbour lists
  * so that they stay valid while atoms move less than skin / 2 (pairs beyond
  * R + D contribute exactly zero).  hip_stream as for mhc_create.
- * Device memory: about N (3 max_neighbors + 8) doubles and N (2 max_neighbors
- * + 4) ints, plus at most 2 (8N + 64) ints of cells.
+ * Device memory: N (3 max_neighbors + 16) doubles and N (4 max_neighbors + 5)
+ * ints, plus at most 2 (8N + 64) ints of cells (and 8 KiB).
  * Errors: INVALID_ARG, OOM, HIP (mhc_virial_last_error(NULL)). */
 mhc_status mhc_virial_create(int device, void *hip_stream, int64_t n_atoms, const double *mass_amu,
                              const double *box, const mhc_tersoff_params *params, int32_t max_neighbors,
