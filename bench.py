@@ -136,6 +136,17 @@ def profiled_traffic(workload, kernel):
     return None
 
 
+def per_step_record(N, M, n_md, wall, kernel_ms):
+    """The per-step FP32 path over n_md MD steps: wall seconds, and what the
+    contraction kernels reach of the float32 vector rate in their summed time
+    (the steps of a push share passes over the basis: no rate of bytes per step)."""
+    units = float(N) * M * n_md
+    tflops = FLOP_PER_UNIT * units / (kernel_ms * 1e-3) / 1e12 if kernel_ms > 0 else None
+    return {"value": units / wall, "unit": "atom*mode*steps/s", "md_steps": n_md, "ms_per_md_step": wall / n_md * 1e3,
+            "kernel_TFLOPs": tflops,
+            "kernel_frac": tflops * 1e12 / PEAK_FP32_VALU_FLOPS if tflops is not None else None}
+
+
 def count_bins(freq, nb):
     """Bins of equal mode counts in frequency order (stable for equal frequencies)."""
     import numpy as np
@@ -965,7 +976,7 @@ def main():
     bW = [W[i * md_per_step:(i + 1) * md_per_step] for i in range(n_blocks)]
     log(f"inputs: {n_blocks} blocks resident ({n_blocks * bytes_per_block / 1e9:.2f} GB)")
     wall, launches, kms = time_pushes(h, bv, bW, args.warmup, K)
-    sched_used = h.last_schedule()
+    sched_used, kernel = h.last_schedule(), h.last_kernel()
     units = float(N) * M * md_per_step * K
     value = units / wall
     avg_ms = kms / max(launches, 1)
@@ -983,9 +994,6 @@ def main():
         roof = {"bound": "valu", "achieved": flops / (avg_ms * 1e-3) / 1e12, "peak": PEAK_FP32_VALU_FLOPS / 1e12,
                 "unit": "TFLOP/s", "work": "24 FLOP per atom*mode*step (Eq. 13: 3 FMAs; Eq. 16 bracket: 9 FMAs)"}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    kernel = "k_gemv_steps" if t_block == 1 else {1: "k_gemm", 2: "k_gemm", 3: "k_gemm_split"}.get(sched_used, "k_gemm")
-    if t_block > 1 and (methods & 4) and prec in (0, 1):
-        kernel = "k_gemm_dir"          # the direction split as one contraction
     roof["traffic"] = profiled_traffic(args.workload, kernel)
     roof["traffic_unit"] = "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, calibrated)"
     roof["kernel"] = kernel
@@ -1030,11 +1038,8 @@ def main():
         h2.close()
         del v2, W2
         torch.cuda.empty_cache()
-        v_fp32 = float(N) * M * n_md / wall2
-        out["fp32_per_step"] = {"value": v_fp32, "unit": "atom*mode*steps/s", "md_steps": n_md,
-                                "ms_per_md_step": wall2 / n_md * 1e3,
-                                "hbm_GBps": 12.0 * N * M * n_md / (k2 * 1e-3) / 1e9 if k2 > 0 else None}
-        out["speedup_vs_fp32_per_step"] = value / v_fp32
+        out["fp32_per_step"] = per_step_record(N, M, n_md, wall2, k2)
+        out["speedup_vs_fp32_per_step"] = value / out["fp32_per_step"]["value"]
 
     if not args.no_cpu_baseline:
         log("cpu baseline (oracle)")
