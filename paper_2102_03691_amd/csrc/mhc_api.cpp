@@ -82,6 +82,7 @@ struct PinnedSlab {
 };
 std::mutex g_pinned_mu;
 PinnedSlab* g_pinned = nullptr;
+int g_readers = 0;   // objects between PinnedReads::start and release
 
 }  // namespace
 
@@ -126,6 +127,26 @@ void pinned_release(double* buffer) {
   *at = s->next;
   (void)hipHostFree(s->base);
   delete s;
+}
+
+void PinnedReads::start(size_t device_bytes) {
+  if (open) return;
+  open = true;
+  int readers;
+  {
+    std::lock_guard<std::mutex> lock(g_pinned_mu);
+    readers = ++g_readers;
+  }
+  buf = pinned_acquire(device_bytes >= PINNED_LARGE || readers >= PINNED_SHARED);
+}
+
+void PinnedReads::release() {
+  pinned_release(buf);
+  buf = nullptr;
+  if (!open) return;
+  open = false;
+  std::lock_guard<std::mutex> lock(g_pinned_mu);
+  --g_readers;
 }
 
 double* PinnedReads::buffer(size_t bytes) {
@@ -806,7 +827,9 @@ static mhc_status finalize_impl(mhc_ctx* ctx) {
   ctx->R3 = R3;
   ctx->d_out = reinterpret_cast<double*>(pout);
   ctx->finalized = true;
-  return mhc_reset(ctx);
+  st = mhc_reset(ctx);
+  if (!st) ctx->reads.start(ctx->bytes);
+  return st;
 }
 
 mhc_status mhc_reset(mhc_ctx* ctx) {

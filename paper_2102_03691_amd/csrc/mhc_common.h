@@ -240,20 +240,23 @@ constexpr size_t kPinnedBytes = size_t(64) << 10;
 double* pinned_acquire(bool allocate);
 void pinned_release(double* buffer);
 
-// The pinned buffer of one object's reads.  A first read takes one that is
-// there, or none (the copy makes it 8 us longer); the allocation comes with the
-// second, so that an object that is made, read once and destroyed, the only one
-// of its process, does not pay for it (a per-step context of 64 atoms from
-// create to destroy 207 us, with the allocation in finalize 260; an SHC object
-// of 216 atoms 105 and 122 us).
+// The pinned buffer of one object's reads.  Alone in its process it would pay for
+// the allocation on its own, so an object is made with a buffer only where that
+// is lost beside its other costs (PINNED_LARGE bytes of device memory), shared
+// (from the PINNED_SHARED-th object alive) or nothing (one is free).  Otherwise
+// its first read is copied (8 us longer) and the second allocates: an object
+// that is made, read once and destroyed does not pay.  A per-step context of 64
+// atoms from create to destroy 207 us, with the allocation in finalize 260; an
+// SHC object of 216 atoms 105 and 122 us.
+constexpr size_t PINNED_LARGE = size_t(16) << 20;
+constexpr int PINNED_SHARED = 8;
 struct PinnedReads {
   double* buf = nullptr;
+  bool open = false;
   int64_t n_reads = 0;   // of those that found no buffer
-  double* buffer(size_t bytes);   // null: copy from device memory
-  void release() {
-    pinned_release(buf);
-    buf = nullptr;
-  }
+  void start(size_t device_bytes);   // the object is ready
+  double* buffer(size_t bytes);      // null: copy from device memory
+  void release();
 };
 
 // Read-out of the GKMA accumulators: C = (csum + ccomp [+ psum + pcomp]) /

@@ -230,6 +230,7 @@ mhc_status mhc_shc_create(int device, void* hip_stream, int64_t n_atoms, int32_t
       hipMemsetAsync(c->ksum, 0, (size_t)n_lags * 9 * 2 * 8, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess)
     return bail(MHC_ERR_HIP, "initial clear");
+  c->reads.start(ring_bytes + vt_bytes + (size_t)t_block * c->N3 * 16);
   *out = c;
   return MHC_OK;
 }
