@@ -20,8 +20,8 @@ def _gpu():
 
 
 @pytest.mark.parametrize("max_nb", [4, 20])
-@pytest.mark.parametrize("edge", [30.0, 700.0])     # 10^3 cells, and 233 x 233 x 116 (6 per atom)
-def test_device_memory_is_as_stated(edge, max_nb):
+@pytest.mark.parametrize("edge,cells", [(30.0, 10 * 10 * 10), (700.0, 233 * 233 * 116)])   # the last: 6 per atom, of at most 8
+def test_device_memory_is_as_stated(edge, cells, max_nb):
     import torch
     from paper_2102_03691_amd import ModalVirial, tersoff_si
     announce(f"virial memory edge={edge} max_nb={max_nb}")
@@ -30,7 +30,7 @@ def test_device_memory_is_as_stated(edge, max_nb):
     d, i, j = map(int, re.search(r"Device memory: (?:about )?N \(3 max_neighbors \+ (\d+)\) doubles and "
                                  r"N \((\d+) max_neighbors \+ (\d+)\) ints", text).groups())
     N = 1 << 20
-    mass, cells = np.full(N, 28.0), min(int(edge // 3) ** 3, 8 * N + 64)
+    mass = np.full(N, 28.0)
     stated = N * ((3 * max_nb + d) * 8 + (i * max_nb + j) * 4) + 2 * cells * 4 + 8192
     used = []
     for _ in range(2):                              # the first turn warms the runtime
