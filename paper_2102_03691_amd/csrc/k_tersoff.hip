@@ -11,15 +11,14 @@
 //
 // Pipeline (deterministic: fixed summation orders, sorted lists):
 //   neighbours (every few MD steps): cell of each atom (counting sort with
-//     atomics), exclusive scan of the cell counts (per-block sums, their
-//     scan, per-block scans), cell fill, per-atom scan of the 27 surrounding
-//     cells (minimum image, r < R + D + skin), list sorted by atom index (so
-//     the result does not depend on the order the atomics filled the cells),
-//     reverse slots (where i sits in j's list);
+//     atomics), exclusive scan of the cell counts, the atoms and their
+//     positions by cell, per atom a scan of the 27 surrounding cells by
+//     sixteen lanes (minimum image, r < R + D + skin), list sorted by atom
+//     index (so the result does not depend on the order the atomics filled the
+//     cells), reverse slots (where i sits in j's list);
 //   per evaluation, LPA lanes per atom (one per neighbour slot, LPA the
-//     next power of two >= the largest neighbour count, at least 4; the site
-//     kernel runs 4 lanes x 2 slots where LPA is 8), the pair values of an
-//     atom shared through LDS:
+//     next power of two >= the largest neighbour count, at least 4; where LPA
+//     is 8, 4 lanes x 2 slots), the pair values of an atom shared through LDS:
 //     k_tersoff_site -- pair vector, f_C, the two exponentials, zeta_ij,
 //       b_ij, db_ij/dzeta_ij; U_i (summed in slot order by the first lane);
 //       the partial dU_i/dr_ij of the lane's pair;
@@ -1160,8 +1159,11 @@ hipError_t launch_md_nvt_start(hipStream_t s, double* pos, double* vel, const do
                                const double* from, double* to, const ThermostatArgs& th, int mode, const double* ref,
                                double thr2, int* need) {
   // Summing the partials in every work-group is cheaper than a launch while
-  // there are few of them (512: 16384 atoms, 256 work-groups); the reads grow
-  // with the square of the size.
+  // there are few of them; the reads grow with the square of the size.  An NVT
+  // step with the launch / without, us: 512 atoms (16 partials) 16.1 / 14.1,
+  // 8000 (250) 18.7 / 16.8, 16224 (507) 19.2 / 17.4, 32768 (1024) 22.2 / 21.3,
+  // 64000 (2000) 29.8 / 30.1, 216000 (6750) 58 / 68.  The line is short of the
+  // crossing, which lies between 1024 and 2000.
   constexpr int64_t INLINE_PARTS = 512;
   if (n_part > INLINE_PARTS) {
     const hipError_t e = launch_thermostat(s, part, n_part, from, to, th, mode);

@@ -617,11 +617,13 @@ mhc_status group_block(mhc_shc_group* g, const float* const* v, const float* con
   GHIP_TRY(hipEventRecord(g->ev[slot], g->stream), "event record");
   g->ev_pending[slot] = true;
   GHIP_TRY(launch_shc_ring_group(g->stream, d, n, rb, t_count), "virial rings");
-  // Work-groups of one length: an eighth of them in a row to each XCD (64
-  // systems of 100 atoms 247 us, dealt out 270 us).  Else the tiles of one dof
-  // range, at least 24 work-groups, dealt to the XCDs in turn: the XCDs end
-  // together (32 systems of 216 to 1000 atoms 647 -> 629 us, 4 of 216 to 1000
-  // atoms 148 -> 105 us).
+  // Work-groups of one length: an eighth of them in a row to each XCD, whose
+  // tiles then share its L2.  Else the tiles of one dof range, at least 24
+  // work-groups, dealt to the XCDs in turn: the XCDs end together.  A push of
+  // 256 steps, 250 lags, eighths / dealt, us: 5 systems of 500 atoms 115 / 126,
+  // 64 of 100 411 / 419, 16 of 1000 517 / 527; 32 of 216 to 1000 881 / 629, 4 of
+  // 216 to 1000 145 / 108, 24 of 100 to 1940 1034 / 885, 6 of 64 to 2000 236 /
+  // 216.  (The same sides at 64 to 600 lags and 64 to 512 steps.)
   const int tiles = (int)(shc_gram_wgs(t_count, g->sys[fused[0]]->n_lags, 1) / 3);
   const bool even = g->sys[fused.front()]->dk == g->sys[fused.back()]->dk && wg % 8 == 0;
   GHIP_TRY(launch_shc_gram_group(g->stream, d, n, wg, even ? (int)(wg / 8) : (23 + tiles) / tiles * tiles),
