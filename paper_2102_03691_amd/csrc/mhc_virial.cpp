@@ -42,7 +42,7 @@ struct mhc_virial {
   CellGrid cg{};
   bool lists_ok = false;
 
-  void* mem = nullptr;      // the device buffers below, one allocation
+  std::vector<void*> allocs;   // of the device buffers below
   double* h_read = nullptr; // pinned, 64 bytes of it: bond flags and thermostat read back, the search's flags (last 16)
   double* d_mass = nullptr;
   NeighborBufs nb{};
@@ -128,21 +128,32 @@ mhc_status venter(mhc_virial* v) {
 }
 
 void vfree(mhc_virial* v) {
-  if (v->mem) (void)hipFree(v->mem);
-  v->mem = nullptr;
+  for (void* p : v->allocs) (void)hipFree(p);
+  v->allocs.clear();
   pinned_release(v->h_read);
   v->h_read = nullptr;
 }
 
-// Parts of one device allocation (a hipMalloc and hipFree each for two dozen
-// took 15 us longer an object); base null: sizes only.
+// The arrays of an object as parts of device allocations of at most `limit`
+// bytes (an array larger than that has its own): one allocation where that is up
+// to 64 MB, which the runtime keeps for the next (a hipMalloc and hipFree for
+// each of two dozen arrays took 15 us longer an object of 512 atoms, 110 us
+// longer one of 27000), or where an array alone is larger (216000 atoms: create
+// to destroy 1.7 -> 1.0 ms); else an allocation an array (64000 atoms: 420 us;
+// in one 574, in two of up to 64 MB 620, because the runtime then gives a large
+// one back to the system).
 struct Parts {
-  char* base = nullptr;
-  size_t bytes = 0;
+  static constexpr size_t PIECE = size_t(64) << 20;
+  size_t limit = PIECE, largest = 0;
+  std::vector<size_t> size{0};          // of each allocation
+  const std::vector<void*>* base = nullptr;   // the allocations (null: sizes only)
   template <class T>
   void take(size_t count, T** out) {
-    if (base) *out = reinterpret_cast<T*>(base + bytes);
-    bytes += (std::max<size_t>(count * sizeof(T), 1) + 255) / 256 * 256;
+    const size_t n = (std::max<size_t>(count * sizeof(T), 1) + 255) / 256 * 256;
+    largest = std::max(largest, n);
+    if (size.back() > 0 && size.back() + n > limit) size.push_back(0);
+    if (base) *out = reinterpret_cast<T*>(static_cast<char*>((*base)[size.size() - 1]) + size.back());
+    size.back() += n;
   }
 };
 
@@ -247,8 +258,7 @@ mhc_status mhc_virial_create(int device, void* hip_stream, int64_t n_atoms, cons
   const int64_t N = n_atoms, MN = (int64_t)max_neighbors * N;
   const int64_t n_cells = (int64_t)v->cg.nc[0] * v->cg.nc[1] * v->cg.nc[2];
   NeighborBufs& b = v->nb;
-  auto carve = [&](char* base) {
-    Parts m{base};
+  auto carve = [&](Parts& m) {
     m.take(N, &v->d_mass), m.take(MN, &b.nbr), m.take(MN, &b.rev), m.take(N, &b.n_nb);
     m.take(N, &b.cell_of), m.take(N, &b.place), m.take(N, &b.atoms), m.take(3 * N, &b.cpos);
     m.take(n_cells, &b.count), m.take(n_cells + 1, &b.start), m.take((n_cells + 1023) / 1024, &b.tile_sums);
@@ -257,14 +267,27 @@ mhc_status mhc_virial_create(int device, void* hip_stream, int64_t n_atoms, cons
     m.take(3 * N, &v->d_pos2), m.take(std::max(md_nvt_parts(N), gather_parts(N, 64)), &v->d_kepart);
     m.take(MN, &v->bb.nbr), m.take(MN, &v->bb.rev), m.take(N, &v->bb.n_nb), m.take(N, &v->bb.mask);
     m.take(3 * N, &v->bb.ref), m.take(12, &v->bb.flags);
-    return m.bytes;
   };
-  if (hipMalloc(&v->mem, carve(nullptr)) != hipSuccess) {
-    (void)hipGetLastError();
-    v->mem = nullptr;
-    return cleanup(MHC_ERR_OOM, "device allocation failed");
+  Parts plan;
+  carve(plan);
+  if (plan.size.size() > 1) {
+    const size_t limit = plan.largest > Parts::PIECE ? SIZE_MAX : 0;
+    plan = Parts{};
+    plan.limit = limit;
+    carve(plan);
   }
-  (void)carve(static_cast<char*>(v->mem));
+  for (size_t bytes : plan.size) {
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return cleanup(MHC_ERR_OOM, "device allocation failed");
+    }
+    v->allocs.push_back(p);
+  }
+  Parts place;
+  place.limit = plan.limit;
+  place.base = &v->allocs;
+  carve(place);
   if (!(v->h_read = pinned_acquire(true))) return cleanup(MHC_ERR_OOM, "pinned allocation failed");
   // the search's kernels write their three results straight into the last 16
   // bytes of the pinned buffer: no copy behind the search
